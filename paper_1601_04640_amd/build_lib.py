@@ -40,6 +40,11 @@ def _jobs(build_dir=BUILD, extra=()):
         obj = os.path.join(build_dir, f"batch_{real}.o")
         jobs.append((obj, [HIPCC, *FLAGS, *extra, f"-DGP_REAL={real}", "-c",
                            os.path.join(CSRC, "gp_batch_inst.hip"), "-o", obj]))
+    for real in ("float", "double"):
+        obj = os.path.join(build_dir, f"sweep_{real}.o")
+        jobs.append((obj, [HIPCC, *FLAGS, *extra, f"-DGP_REAL={real}",
+                           f"-DGP_SWEEP_FP32={int(real == 'float')}", "-c",
+                           os.path.join(CSRC, "gp_sweep_inst.hip"), "-o", obj]))
     obj = os.path.join(build_dir, "capi.o")
     jobs.append((obj, [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, "gp_capi.hip"), "-o", obj]))
     # host-only code over the public C ABI (saved states, output cadence)

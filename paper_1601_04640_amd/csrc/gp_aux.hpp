@@ -67,58 +67,108 @@ __device__ inline zd zinv(zd a) {
 // They depend on the factors only: the products g of every chunk, composed across the
 // lanes in the solve's own step order.
 constexpr int kScanWeights = 2 * 5 * 32;  // 2 NS P for P <= 32
+// Lane q < P holds chunk q's product in gc[q]; G, H: LDS of 32 values (every lane of the
+// wave calls it).
 template <typename T>
-__device__ inline void cn_scan_weights(const zd* gc, int P, cpx<T>* w) {
+__device__ inline void cn_scan_weights(const zd* gc, int P, cpx<T>* w, zd* G, zd* H) {
   const int PR = P < 16 ? P : 16;  // lanes of a line inside one row of 16
+  const int q = threadIdx.x;
   int NS = 0;
   while ((1 << NS) < P) ++NS;
-  zd G[32], H[32];
   for (int dir = 0; dir < 2; ++dir) {
-    for (int q = 0; q < P; ++q) G[q] = gc[q];
+    if (q < P) G[q] = gc[q];
+    __syncthreads();
     int s = 0;
     for (int off = 1; off < PR; off <<= 1, ++s) {
-      for (int q = 0; q < P; ++q) {
+      if (q < P) {
         w[(dir * NS + s) * P + q] = cpx<T>{(T)G[q].re, (T)G[q].im};
         const int rq = q % PR;
         const bool take = dir == 0 ? rq >= off : rq + off < PR;
         H[q] = take ? zmul(G[q], G[dir == 0 ? q - off : q + off]) : G[q];
       }
-      for (int q = 0; q < P; ++q) G[q] = H[q];
+      __syncthreads();
+      if (q < P) G[q] = H[q];
+      __syncthreads();
     }
-    if (P == 32)  // the step across the two rows of a 32-lane line
-      for (int q = 0; q < P; ++q) w[(dir * NS + s) * P + q] = cpx<T>{(T)G[q].re, (T)G[q].im};
+    if (P == 32 && q < P)  // the step across the two rows of a 32-lane line
+      w[(dir * NS + s) * P + q] = cpx<T>{(T)G[q].re, (T)G[q].im};
+    __syncthreads();
   }
 }
 
-// Third set: A = -i Ar, the adjoint sweep of a real-time step (conjugate factors).
+// One block of one wave per set; third set: A = -i Ar, the adjoint sweep of a real-time step
+// (conjugate factors).  The recurrence of c is serial, but it reaches its fixed point, to the
+// last bit, after a few dozen rows unless A is large: from there on every factor is the same
+// and the wave's lanes write them (256 rows in FP64: 150 us by one thread).  A line that has
+// not got there by kCnHead rows goes on row by row.
+constexpr int kCnHead = 1024;
 template <typename T>
-__global__ void k_cn_tables(cpx<T>* m_im, cpx<T>* m_re, cpx<T>* m_adj, int N, double Ar, int P) {
-  if (blockIdx.x != 0 || threadIdx.x > 2) return;
-  const int set = threadIdx.x;
+__global__ void __launch_bounds__(64) k_cn_tables(cpx<T>* m_im, cpx<T>* m_re, cpx<T>* m_adj, int N,
+                                                  double Ar, int P) {
+  __shared__ zd cs[kCnHead];  // c_1 .. c_head
+  __shared__ zd gc[32], G[32], H[32];
+  __shared__ int head_s;
+  const int set = blockIdx.x, lane = threadIdx.x;
+  if (set > 2) return;
   cpx<T>* mt = set == 0 ? m_im : (set == 1 ? m_re : m_adj);
   const zd A = set == 0 ? zd{Ar, 0.0} : (set == 1 ? zd{0.0, Ar} : zd{0.0, -Ar});
   const zd a = {-A.re, -A.im};
   const zd b = {1.0 + 2.0 * A.re, 2.0 * A.im};
+  const zd A2 = {2.0 * A.re, 2.0 * A.im};
   const int S = (N + P - 1) / P;
+  auto next = [&](zd c) { return zinv(zsub(b, zmul(a, c))); };  // m of the row after c's
   // chunk products of g; a chunk holding a boundary row or reaching past the line end
   // has a zero factor
-  zd gc[32];
-  for (int q = 0; q < P; ++q) {
-    const bool zero = q == 0 || (q + 1) * S > N - 1;
-    gc[q] = zero ? zd{0.0, 0.0} : zd{1.0, 0.0};
+  auto zero_chunk = [&](int q) { return q == 0 || (q + 1) * S > N - 1; };
+  if (lane == 0) {
+    zd c = {0.0, 0.0};
+    int i = 1;
+    bool fixed = false;
+    for (; i <= N - 2 && i <= kCnHead && !fixed; ++i) {
+      const zd n = zmul(a, next(c));
+      fixed = n.re == c.re && n.im == c.im;
+      c = n;
+      cs[i - 1] = c;
+    }
+    head_s = (fixed || i > N - 2) ? i - 1 : -1;  // rows in cs; -1: not at the fixed point
   }
-  zd c = {0.0, 0.0};
-  mt[0] = cpx<T>{0, 0};
-  for (int i = 1; i <= N - 2; ++i) {
-    const zd m = zinv(zsub(b, zmul(a, c)));
-    c = zmul(a, m);
-    const zd f = zmul(zd{2.0 * A.re, 2.0 * A.im}, m);  // the solve's factor 2 A m
-    mt[i] = cpx<T>{(T)f.re, (T)f.im};
-    const int q = i / S;
-    gc[q] = zmul(gc[q], zd{-c.re, -c.im});
+  __syncthreads();
+  const int head = head_s;
+  // c of row i >= 1 (0 for the row before the first)
+  auto c_of = [&](int i) { return i < 1 ? zd{0.0, 0.0} : cs[(i < head ? i : head) - 1]; };
+  if (head >= 0) {
+    for (int i = lane; i < N; i += 64) {
+      cpx<T> f = {0, 0};
+      if (i >= 1 && i <= N - 2) {
+        const zd v = zmul(A2, next(c_of(i - 1)));  // the solve's factor 2 A m
+        f = cpx<T>{(T)v.re, (T)v.im};
+      }
+      mt[i] = f;
+    }
+    for (int q = lane; q < P && P > 1; q += 64) {  // (one lane per line: no scan)
+      zd g = zero_chunk(q) ? zd{0.0, 0.0} : zd{1.0, 0.0};
+      for (int i = q * S; i < (q + 1) * S; ++i)
+        if (i >= 1 && i <= N - 2) {
+          const zd c = c_of(i);
+          g = zmul(g, zd{-c.re, -c.im});
+        }
+      gc[q] = g;
+    }
+  } else if (lane == 0) {
+    for (int q = 0; q < P; ++q) gc[q] = zero_chunk(q) ? zd{0.0, 0.0} : zd{1.0, 0.0};
+    zd c = {0.0, 0.0};
+    mt[0] = cpx<T>{0, 0};
+    for (int i = 1; i <= N - 2; ++i) {
+      const zd m = next(c);
+      c = zmul(a, m);
+      const zd f = zmul(A2, m);
+      mt[i] = cpx<T>{(T)f.re, (T)f.im};
+      gc[i / S] = zmul(gc[i / S], zd{-c.re, -c.im});
+    }
+    mt[N - 1] = cpx<T>{0, 0};
   }
-  mt[N - 1] = cpx<T>{0, 0};
-  cn_scan_weights(gc, P, mt + N);
+  __syncthreads();
+  cn_scan_weights(gc, P, mt + N, G, H);
 }
 
 // Spherical-cutoff factor b(s) = 1 + 3 cos s/s^2 - 3 sin s/s^3 (s = kR); for s < 1 the

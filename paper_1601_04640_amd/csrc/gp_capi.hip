@@ -18,6 +18,7 @@
 #include "gp_generic_launch.hpp"
 #include "gp_kernels.hpp"
 #include "gp_launch.hpp"
+#include "gp_sweep_launch.hpp"
 
 using namespace gpdbec;
 
@@ -83,11 +84,14 @@ struct Layout {
   // segments over the strided columns (a long y axis, or one-line y axes past a tile
   // with a segment length dividing them; others run on a transposed copy in o_gscr)
   bool lx, ly, sy;
+  // the y and z sweeps (axes 1, 2) over strided columns; S = 0: another form
+  SweepCfg sw[3];
   GLong lg[2];
   GLX lxg;  // the long-x passes' geometry (host side; the plans' strides from lg)
   // byte offsets inside the workspace
   size_t o_psi, o_V, o_spec, o_ktab, o_tw[3], o_blue[3], o_cn[3][3], o_px[2], o_pnl, o_pcol, o_padj, o_sfield,
       o_scalars, o_ring, o_obs, o_io, o_stamps, o_stage, o_gscr, total;
+  size_t o_sw[3][3];  // the sweeps' gain tables per axis and factor set
   // long axes: stage twiddles of the A- and B-point plans and W_N^m, their Bluestein
   // tables, the segments' carry products per factor set, segment summaries and carries
   size_t o_ltw[2][3], o_lblue[2][2], o_seg[2][3], o_ssum, o_scar;
@@ -153,6 +157,14 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
   const int H = L.n0 / 2 + 1;
   L.nspec = (size_t)H * L.n1 * L.n2;
   L.generic = is_generic(p);
+  if (L.generic) {
+    const long long row = L.n0, plane = (long long)L.n0 * L.n1;
+    L.sw[1] = fp64 ? SweepLaunch<double>::cfg(L.n1, L.n0, L.n2, row)
+                   : SweepLaunch<float>::cfg(L.n1, L.n0, L.n2, row);
+    if (p->geom == GP_3D)
+      L.sw[2] = fp64 ? SweepLaunch<double>::cfg(L.n2, L.n0, L.n1, plane)
+                     : SweepLaunch<float>::cfg(L.n2, L.n0, L.n1, plane);
+  }
   const int ns0[2] = {L.n0, L.n1};
   bool lng[2] = {false, false};
   for (int a = 0; a < 2 && p->geom != GP_3D; ++a)
@@ -163,7 +175,7 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
   // one-line y axes past a tile: segmented when there are enough column segments to fill
   // the GPU (the summary walks each with one thread; fewer ran slower than the transposed
   // sweep: 1500^2 FP32 0.12 -> 0.22 ms, while 8192^2 went 3.07 -> 2.75 ms)
-  if (!L.ly && p->geom != GP_3D && L.generic && L.n1 > kTileMaxN) {
+  if (!L.ly && p->geom != GP_3D && L.generic && !L.sw[1].S && L.n1 > kTileMaxN) {
     GLong sg{};
     if (gen_seg_split(L.n1, &sg.sn, &sg.nseg) &&
         (long long)L.n0 * sg.nseg >= (fp64 ? 16384 : 40960)) {
@@ -192,7 +204,9 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
     L.nb_nl = fp64 ? GLaunch<double>::nl_blocks(L.n0, L.n1, L.n2)
                    : GLaunch<float>::nl_blocks(L.n0, L.n1, L.n2);
     // blocks of the last sweep (z in 3D, y in 2D), which the z observe shares
-    L.nb_col = p->geom == GP_3D
+    const int last = p->geom == GP_3D ? 2 : 1;
+    L.nb_col = L.sw[last].S ? L.sw[last].blocks
+               : p->geom == GP_3D
                    ? (fp64 ? GLaunch<double>::cn_blocks(L.n2, L.n0 * L.n1, true)
                            : GLaunch<float>::cn_blocks(L.n2, L.n0 * L.n1, true))
                    : (fp64 ? GLaunch<double>::cn_blocks(
@@ -202,9 +216,9 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
     // a scratch grid for the one-thread-per-line sweeps (3D grids whose y or z sweep has
     // many lines longer than a tile) and for the transposed 2D y sweep of long lines
     L.gscr = p->geom == GP_3D
-                 ? (GLaunch<float>::cn_by_columns(L.n1, true, L.n0 * L.n2) ||
-                    GLaunch<float>::cn_by_columns(L.n2, true, L.n0 * L.n1))
-                 : ((GLaunch<float>::y2d_transposed(L.n1) && !L.sy) || L.lx);
+                 ? ((!L.sw[1].S && GLaunch<float>::cn_by_columns(L.n1, true, L.n0 * L.n2)) ||
+                    (!L.sw[2].S && GLaunch<float>::cn_by_columns(L.n2, true, L.n0 * L.n1)))
+                 : ((!L.sw[1].S && GLaunch<float>::y2d_transposed(L.n1) && !L.sy) || L.lx);
     // a segmented y sweep (the last in 2D) runs over the strided columns
     if (L.sy)
       L.nb_col = fp64 ? GLaunch<double>::seg_blocks(L.lg[1].sn, L.n0 * L.lg[1].nseg, true)
@@ -245,6 +259,8 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
     L.o_blue[a] = take(!la && ms != ns[a] ? 2 * L.esz * (size_t)(ns[a] + ms) : 0);
     // factor table and scan weights per set (imaginary time, real time, adjoint)
     for (int t = 0; t < 3; ++t) L.o_cn[a][t] = take(2 * L.esz * (ns[a] + kScanWeights));
+    for (int t = 0; t < 3; ++t)
+      L.o_sw[a][t] = take(2 * L.esz * SweepLaunch<float>::table_len(L.sw[a]));
   }
   // Partial-sum slots: one per tile, for the largest tile count any shape variant of the
   // batched passes can use (x and column tiles of 8 lines).
@@ -582,6 +598,12 @@ struct Passes {
     const cpx<T>* f = mode == 2 ? nullptr : cn(c, axis, k);
     const long long plane = (long long)L.n0 * L.n1;
     cpx<T>* dscr = c->at<cpx<T>>(L.o_gscr);
+    if (L.sw[axis].S) {  // y or z over the strided columns (2D: one outer index)
+      const int n = axis == 1 ? L.n1 : L.n2;
+      return dev(SweepLaunch<T>::run(L.sw[axis], mode, k != 0, c->st, psi(c), f,
+                                     c->at<cpx<T>>(L.o_sw[axis][k]), pc, n, L.n0,
+                                     axis == 1 ? L.n0 : plane, axis == 1 ? plane : L.n0));
+    }
     if (axis == 0 && L.lx)  // long x lines: segmented
       return dev(GLaunch<T>::seg_sweep(mode, c->st, psi(c), L.lg[0].sn, L.lg[0].nseg, L.n1, f,
                                        c->at<cpx<T>>(L.o_seg[0][k]), c->at<cpx<T>>(L.o_ssum),
@@ -948,9 +970,17 @@ struct Passes {
       // in the strided sweeps
       const int P = L.generic ? 1
                               : kThreads / (a == 0 ? Launch<T>::tj(ns[a]) : Launch<T>::tc(ns[a]));
-      hipLaunchKernelGGL(k_cn_tables<T>, dim3(1), dim3(64), 0, c->st,
+      hipLaunchKernelGGL(k_cn_tables<T>, dim3(3), dim3(64), 0, c->st,
                          c->at<cpx<T>>(L.o_cn[a][0]), c->at<cpx<T>>(L.o_cn[a][1]),
                          c->at<cpx<T>>(L.o_cn[a][2]), ns[a], Ar, P);
+      if (L.sw[a].S) {
+        SweepTables t{};
+        for (int k = 0; k < 3; ++k) {
+          t.f[k] = c->at<cpx<T>>(L.o_cn[a][k]);
+          t.w[k] = c->at<cpx<T>>(L.o_sw[a][k]);
+        }
+        GP_HIP(SweepLaunch<T>::gains(L.sw[a], c->st, t, ns[a]));
+      }
       if (a == 0 ? L.lx : (a == 1 && L.sy)) {  // the segments' fixed numbers per factor set
         for (int t = 0; t < 3; ++t)
           hipLaunchKernelGGL(k_seg_tables<T>, dim3(blocks_for(L.lg[a].nseg)), dim3(kThreads), 0,

@@ -20,6 +20,7 @@
 //                   chunks' values in registers); the x sweep with the nonlinear
 //                   sub-step applied as it loads; optionally with the norm and
 //                   difference sums of the new state
+//                   (the y and z sweeps of lines up to 2048 points: gp_sweep.hpp)
 //   kg_cn_cols      the same sweep, one thread per strided line with the recurrence
 //                   values in a scratch grid: strided axes of more than 1024 points with
 //                   many lines, where consecutive threads read consecutive addresses

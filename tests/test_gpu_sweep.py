@@ -1,0 +1,101 @@
+"""Strided Crank-Nicolson sweeps (gp_sweep.hpp): every chunk and column shape, at the edges of
+its range, on states whose step is known line by line.
+
+Without couplings and trap a step of a product state X(x) Y(y) Z(z) is the product of the
+three one-dimensional Crank-Nicolson steps, which scipy's banded solver gives in FP64.  A
+sweep's error is a few roundings of the increment; three sweeps are held to 64 units in the
+last place of the largest value per step, norm and kinetic energy of the record to twice that of their own scale."""
+import numpy as np
+import pytest
+import scipy.linalg
+
+pytestmark = pytest.mark.gpu
+
+# geometry, lengths, precision: at least one length outside the specialised set
+SHAPES = [
+    ("3d", (18, 9, 8), "fp32"),        # one chunk and one row over; fewer columns than a tile
+    ("3d", (33, 17, 16), "fp32"),      # a column over a tile
+    ("3d", (34, 66, 130), "fp32"),     # several waves
+    ("3d", (18, 22, 1030), "fp32"),    # 16-row chunks, z lines past 1024 points
+    ("2dxy", (50, 1025, 1), "fp32"),   # 16-row chunks, half the columns
+    ("2dxy", (21, 2047, 1), "fp32"),   # the longest lines
+    ("3d", (18, 9, 8), "fp64"),
+    ("3d", (34, 17, 66), "fp64"),
+    ("3d", (18, 62, 520), "fp64"),     # 16 columns per block
+    ("2dxz", (50, 1, 1022), "fp64"),   # quarter-width tiles
+    ("2dxy", (50, 1026, 1), "fp64"),   # 16-row chunks, quarter-width tiles
+    ("2dxy", (21, 2048, 1), "fp64"),   # the longest lines
+    ("3d", (301, 290, 200), "fp64"),   # an array past 256 MiB with a ragged pitch
+]
+
+
+def _line(n, seed):
+    rng = np.random.default_rng(seed)
+    x = np.linspace(-2.5, 2.5, n)
+    v = np.exp(-x * x) * np.exp(1j * 0.7 * x) * (1 + 0.01 * rng.uniform(-1, 1, n))
+    v[0] = v[-1] = 0
+    return v
+
+
+def _cn(v, h, dt, imag):
+    a = dt / (4 * h * h) * (1.0 if imag else 1j)
+    n = v.size - 2
+    band = np.zeros((3, n), complex)
+    band[0, 1:] = band[2, :-1] = -a
+    band[1] = 1 + 2 * a
+    rhs = (1 - 2 * a) * v[1:-1] + a * (v[:-2] + v[2:])
+    out = np.zeros_like(v)
+    out[1:-1] = scipy.linalg.solve_banded((1, 1), band, rhs)
+    return out
+
+
+@pytest.mark.parametrize("imag", [True, False], ids=["imag", "real"])
+@pytest.mark.parametrize("geom,n,prec", SHAPES, ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))
+def test_free_product_state(geom, n, prec, imag):
+    import torch
+    from paper_1601_04640_amd.binding import Solver
+    print(geom, n, prec, imag, flush=True)
+    h = [0.11, 0.13, 0.12]
+    w = dict(geom=geom, nx=n[0], ny=n[1], nz=n[2], dx=h[0], dy=h[1], dz=h[2], dt=0.003, gamma=0.0,
+             nu=1.0, lam=1.0, g=0.0, gdd=0.0, R=0.0)
+    axes = {"3d": (2, 1, 0), "2dxy": (1, 0), "2dxz": (2, 0)}[geom]   # array order
+    lines = [_line(n[a], 40 + a) for a in axes]
+    cell = np.prod([h[a] for a in axes])
+    lines[0] /= np.sqrt(np.prod([np.sum(np.abs(v) ** 2) for v in lines]) * cell)
+    ct, rt = (torch.complex128, torch.float64) if prec == "fp64" else (torch.complex64, torch.float32)
+
+    def outer(vs):
+        t = torch.ones((), dtype=torch.complex128, device="cuda:0")
+        for v in vs:
+            t = t[..., None] * torch.from_numpy(v).to("cuda:0")
+        return t
+
+    s = Solver(w, prec=prec)
+    s.set_potential(torch.zeros(s.shape, dtype=rt, device="cuda:0"))
+    s.set_psi(outer(lines).to(ct))
+    steps = 3
+    (s.step_imag if imag else s.step_real)(steps)
+    for _ in range(steps):
+        lines = [_cn(v, h[a], w["dt"], imag) for v, a in zip(lines, axes)]
+    norm = np.prod([np.sum(np.abs(v) ** 2) for v in lines]) * cell
+    if imag:
+        lines[0] /= np.sqrt(norm)
+    ref = outer(lines)
+    got = s.get_psi_device().to(torch.complex128)
+    eps = {"fp32": 2.0 ** -24, "fp64": 2.0 ** -53}[prec]
+    tol = 64 * steps * eps
+    assert float((got - ref).abs().max()) <= tol * float(ref.abs().max())
+    e = s.energy()
+    # energies of the free state: the kinetic sum over the axes
+    kin = 0.0
+    for k, a in enumerate(axes):
+        d = np.sum(np.abs(np.diff(lines[k])) ** 2) / h[a] ** 2
+        for m, v in enumerate(lines):
+            d *= 1.0 if m == k else np.sum(np.abs(v) ** 2)
+        kin += 0.5 * d * cell
+    want = 1.0 if imag else norm
+    assert abs(e["norm"] - want) <= 2 * tol * want
+    # the state's error enters the differences relative to the state, not to the difference
+    peak = max(2.0 / h[a] ** 2 for a in axes)
+    assert abs(e["e_kin"] - kin) <= 2 * tol * (kin + np.sqrt(kin * peak))
+    s.close()

@@ -18,6 +18,7 @@
 #include "gp_generic_launch.hpp"
 #include "gp_kernels.hpp"
 #include "gp_launch.hpp"
+#include "gp_rfft_launch.hpp"
 #include "gp_sweep_launch.hpp"
 
 using namespace gpdbec;
@@ -84,6 +85,9 @@ struct Layout {
   // segments over the strided columns (a long y axis, or one-line y axes past a tile
   // with a segment length dividing them; others run on a transposed copy in o_gscr)
   bool lx, ly, sy;
+  // FFT passes of run-time-length axes with the data in registers between stages
+  // (gp_rfft.hpp); k = 0: the other kernels
+  RAxis ra[3];
   // the y and z sweeps (axes 1, 2) over strided columns; S = 0: another form
   SweepCfg sw[3];
   GLong lg[2];
@@ -92,6 +96,7 @@ struct Layout {
   size_t o_psi, o_V, o_spec, o_ktab, o_tw[3], o_blue[3], o_cn[3][3], o_px[2], o_pnl, o_pcol, o_padj, o_sfield,
       o_scalars, o_ring, o_obs, o_io, o_stamps, o_stage, o_gscr, total;
   size_t o_sw[3][3];  // the sweeps' gain tables per axis and factor set
+  size_t o_rp[3][3];  // FFT programs per axis and kind (RL_*)
   // long axes: stage twiddles of the A- and B-point plans and W_N^m, their Bluestein
   // tables, the segments' carry products per factor set, segment summaries and carries
   size_t o_ltw[2][3], o_lblue[2][2], o_seg[2][3], o_ssum, o_scar;
@@ -184,6 +189,16 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
     }
   }
   L.sy = L.sy || L.ly;
+  // y lines are contiguous in the spectrum, z lines strided (no long axis: those split)
+  if (L.generic && !L.lx && !L.ly) {
+    RAxis a1 = fp64 ? r_axis<double>(L.n1) : r_axis<float>(L.n1);
+    if (fp64 ? RLaunch<double>::contiguous_ok(a1) : RLaunch<float>::contiguous_ok(a1)) L.ra[1] = a1;
+    if (p->geom == GP_3D) {
+      RAxis a2 = fp64 ? r_axis<double>(L.n2) : r_axis<float>(L.n2);
+      if (fp64 ? RLaunch<double>::strided_ok(a2, L.n1) : RLaunch<float>::strided_ok(a2, L.n1))
+        L.ra[2] = a2;
+    }
+  }
   GPlan lpa[2], lpb[2];
   const int lim = fp64 ? gen_max_line<double>() : gen_max_line<float>();
   for (int a = 0; a < 2; ++a)
@@ -254,7 +269,8 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
     // twiddles of the stage length (Bluestein's M for a run-time-length axis with a prime
     // factor above 31), then that axis's chirp (n) and filter (M)
     const bool la = a < 2 && lng[a];
-    const int ms = la ? 0 : (L.generic ? gen_stride(ns[a]) : ns[a]);
+    const int ms = la ? 0 : L.ra[a].k ? L.ra[a].m : (L.generic ? gen_stride(ns[a]) : ns[a]);
+    for (int k = 0; k < 3; ++k) L.o_rp[a][k] = take(L.ra[a].k ? sizeof(RProgram) : 0);
     L.o_tw[a] = take(2 * L.esz * ms);
     L.o_blue[a] = take(!la && ms != ns[a] ? 2 * L.esz * (size_t)(ns[a] + ms) : 0);
     // factor table and scan weights per set (imaginary time, real time, adjoint)
@@ -493,6 +509,9 @@ struct Passes {
   // after every step.
   // long 2D axes: stage twiddles of the A- (q = 0) and B-point (q = 1) plans, W_N^m (q = 2)
   static const cpx<T>* ltw(gp_ctx* c, int a, int q) { return c->at<cpx<T>>(c->L.o_ltw[a][q]); }
+  static const RProgram* rprog(gp_ctx* c, int a, int kind) {
+    return c->at<RProgram>(c->L.o_rp[a][kind]);
+  }
   static cpx<T>* gscr(gp_ctx* c) { return c->at<cpx<T>>(c->L.o_gscr); }
 
   // 2D convolution along y of a spectrum whose x axis or y axis is split (four-step):
@@ -549,21 +568,30 @@ struct Passes {
     }
     if (L.lx || L.ly) return g_conv_y_long(c, scale);
     const GKtab none{0, L.n1, L.n2, fdiv_make((uint32_t)L.n1)};
+    const bool r1 = L.ra[1].k > 0;
     if (c->p.geom == GP_3D) {
       // y lines l = kx n2 + k2 (contiguous); z lines l = kx n1 + k1 (stride n1)
       GP_PASS(c, GP_PASS_FFT_Y_FWD,
-              GLaunch<T>::lines(GL_FWD, c->st, spec(c), L.n1, H * L.n2, 1, L.n1, 0, 1,
+              r1 ? RLaunch<T>::contiguous(c->st, spec(c), H * L.n2, L.ra[1], rprog(c, 1, RL_FWD),
+                                          nullptr, nullptr)
+                 : GLaunch<T>::lines(GL_FWD, c->st, spec(c), L.n1, H * L.n2, 1, L.n1, 0, 1,
                                 c->gplan[1], tw(c, 1), nullptr, none, scale));
       GP_PASS(c, GP_PASS_CONV_Z,
-              GLaunch<T>::lines(GL_CONV, c->st, spec(c), L.n2, H * L.n1, L.n1,
+              L.ra[2].k ? RLaunch<T>::strided(c->st, spec(c), L.n1, H, L.ra[2],
+                                              rprog(c, 2, RL_CONV), Kp(c), scale)
+                        : GLaunch<T>::lines(GL_CONV, c->st, spec(c), L.n2, H * L.n1, L.n1,
                                 (long long)L.n1 * L.n2, 1, L.n1, c->gplan[2], tw(c, 2),
                                 Kp(c), GKtab{1, L.n1, L.n2, fdiv_make((uint32_t)L.n1)}, scale));
       GP_PASS(c, GP_PASS_FFT_Y_INV,
-              GLaunch<T>::lines(GL_INV, c->st, spec(c), L.n1, H * L.n2, 1, L.n1, 0, 1,
+              r1 ? RLaunch<T>::contiguous(c->st, spec(c), H * L.n2, L.ra[1], rprog(c, 1, RL_INV),
+                                          nullptr, nullptr)
+                 : GLaunch<T>::lines(GL_INV, c->st, spec(c), L.n1, H * L.n2, 1, L.n1, 0, 1,
                                 c->gplan[1], tw(c, 1), nullptr, none, scale));
     } else {
       GP_PASS(c, GP_PASS_CONV_Y,
-              GLaunch<T>::lines(GL_CONV, c->st, spec(c), L.n1, H, 1, L.n1, 0, 1, c->gplan[1],
+              r1 ? RLaunch<T>::contiguous(c->st, spec(c), H, L.ra[1], rprog(c, 1, RL_CONV), Kp(c),
+                                          scale)
+                 : GLaunch<T>::lines(GL_CONV, c->st, spec(c), L.n1, H, 1, L.n1, 0, 1, c->gplan[1],
                                 tw(c, 1), Kp(c), GKtab{0, L.n1, 1, fdiv_make((uint32_t)L.n1)},
                                 scale));
     }
@@ -936,6 +964,7 @@ struct Passes {
         }
       }
       GP_HIP(GLaunch<T>::prepare());
+      GP_HIP(RLaunch<T>::prepare());
     }
     const int ns[3] = {L.n0, L.n1, L.n2};
     const double hs[3] = {L.h0, L.h1, L.h2};
@@ -959,6 +988,15 @@ struct Passes {
         plan_tables(c->lplan[a][1], L.o_ltw[a][1], L.o_lblue[a][1]);
         hipLaunchKernelGGL(k_twiddles<T>, dim3(blocks_for(ns[a])), dim3(kThreads), 0, c->st,
                            c->at<cpx<T>>(L.o_ltw[a][2]), ns[a]);   // W_N^m
+      } else if (L.ra[a].k) {
+        GPlan pl{};  // the tables of n-point lines with m-point stages
+        pl.n = L.ra[a].n;
+        pl.m = L.ra[a].m;
+        pl.blue = L.ra[a].blue();
+        plan_tables(pl, L.o_tw[a], L.o_blue[a]);
+        for (int k = 0; k < 3; ++k)
+          GP_HIP(RLaunch<T>::program(c->st, L.ra[a], k, tw(c, a), pl.chirp, pl.filt,
+                                     c->at<RProgram>(L.o_rp[a][k])));
       } else if (L.generic) {
         plan_tables(c->gplan[a], L.o_tw[a], L.o_blue[a]);
       } else {

@@ -1,0 +1,598 @@
+// FFTs of lines whose length is a kernel argument, with the data in registers between the
+// stages: a thread runs whole butterflies of radix up to 16, and LDS only carries values from
+// one stage to the next.
+//
+// A length whose prime factors are at most 13 runs Stockham stages of radices 2..16, as few
+// as possible (200 = 5 x 5 x 8, 400 = 4 x 10 x 10, 240 = 15 x 16).  The first stage reads its
+// operands from global memory and the last one leaves its results there, so an FFT of k
+// stages crosses LDS k - 1 times.  A convolution (transform, product, inverse transform)
+// runs the inverse with the radices in reverse order: the operands of its first stage are
+// then the results of the forward transform's last one, which stay in the same registers
+// through the product.  Other lengths run Bluestein's algorithm (Bluestein, "A linear
+// filtering approach to the computation of discrete Fourier transform", 1970) as such a
+// convolution of a length M >= 2 N - 1: with the chirp c_j = exp(-i pi j^2 / N),
+// X_k = c_k sum_j (x_j c_j) conj(c_(k-j)).
+#pragma once
+#include "gp_device.hpp"
+#include "gp_fdiv.hpp"
+#include "gp_kernels.hpp"  // xcd_tile
+#include "gp_sweep.hpp"    // buffer accesses
+
+namespace gpdbec {
+
+constexpr int kRMaxStages = 6;
+constexpr int kRMaxRadix = 16;
+constexpr int kRThreads = 512;  // largest block
+
+// What a step reads, does to its butterflies' results, and writes.  Every transform runs
+// forward: an inverse one is the conjugate of the forward transform of the conjugate, taken
+// where the values are in registers anyway.
+enum : int {
+  // operands: LDS, or the caller's element e (of n; past the line zero for Bluestein)
+  RI_LDS = 0, RI_PLAIN, RI_CONJ, RI_BLUE, RI_BLUE_CONJ,
+  // results: none of these (one butterfly), or an operation and the first butterfly of the
+  // transform back (the radices reversed): the caller's product, Bluestein's filter, the end
+  // of one Bluestein transform with the product and the start of the next
+  RO_NONE = 0, RO_PRODUCT, RO_FILTER, RO_BLUE_PRODUCT,
+  // destination: LDS, or the caller's element
+  RD_LDS = 0, RD_PLAIN, RD_CONJ, RD_BLUE, RD_BLUE_CONJ
+};
+enum : int { RL_FWD = 0, RL_INV = 1, RL_CONV = 2 };
+
+// One radix stage: butterflies of a line (nb = m / rad), product L of the earlier radices, the
+// multipliers and shifts of the divisions by them (gp_fdiv.hpp), the twiddle stride m / (L rad).
+// One 32-byte scalar read.
+struct alignas(32) RStep {
+  uint8_t rad, in, op, out;
+  int32_t nb, L, ts;
+  uint32_t mnb, ml;
+  uint16_t snb, sl;
+  uint32_t pad;
+  __device__ __forceinline__ FDiv fnb() const { return FDiv{0u, mnb, snb}; }
+  __device__ __forceinline__ FDiv fl() const { return FDiv{0u, ml, sl}; }
+};
+
+// The steps of a line of n points: m = n, or Bluestein's length.  One program per kind of
+// pass; it lives in device memory (uniform reads: the fewer lines it takes, the fewer misses
+// stand in the way of a small grid's few blocks).
+constexpr int kRMaxSteps = 4 * (kRMaxStages - 1) + 1;
+struct alignas(64) RProgram {
+  int n, m, steps, pad;
+  const void* chirp;  // Bluestein: c_j, j < n
+  const void* filt;   // FFT_m of conj(c) wrapped to m, over m
+  RStep st[kRMaxSteps];
+  const void* tw;     // exp(-2 pi i k / m), k < m
+};
+
+// The radices (2..maxr, at most kRMaxStages) of n with the fewest stages, and among those the
+// smallest largest radix (fewest registers); in increasing order.  0: none.
+inline int r_radices(int n, int maxr, int* out) {
+  struct Search {
+    int maxr, best = 0, bestmax = 0;
+    int cur[kRMaxStages], *out;
+    void go(int n, int from, int depth) {
+      if (n == 1) {
+        if (depth == 0) return;
+        const int mx = cur[depth - 1];
+        if (best == 0 || depth < best || mx < bestmax) {
+          best = depth;
+          bestmax = mx;
+          for (int i = 0; i < depth; ++i) out[i] = cur[i];
+        }
+        return;
+      }
+      if (depth >= kRMaxStages || (best && depth + 1 > best)) return;
+      for (int r = from; r <= maxr; ++r) {
+        if (n % r) continue;
+        cur[depth] = r;
+        go(n / r, r, depth + 1);
+      }
+    }
+  } f;
+  f.maxr = maxr;
+  f.out = out;
+  f.go(n, 2, 0);
+  return f.best;
+}
+
+// Stages of an n-point line: k radices for m points (n, or Bluestein's length), by kernels
+// that hold radices up to maxr.  k = 0: none, or a single radix (such short lines take the
+// other kernels).
+struct RAxis {
+  int n = 0, m = 0, k = 0, maxr = 0;
+  int rad[kRMaxStages] = {};
+  bool blue() const { return m != n; }
+};
+
+// Largest radices of the two sets of kernels: FP32 holds every radix up to 16 in 78-108
+// VGPRs; FP64 takes 97-122 with radices up to 10 (4 waves per SIMD) and 115-142 with 11 and
+// 13 (3), so only lengths with such a factor run those.
+template <typename T>
+constexpr int r_max_radix(bool big) { return sizeof(T) == 4 ? 16 : big ? 13 : 10; }
+
+template <typename T>
+inline RAxis r_axis(int n) {
+  RAxis a;
+  a.n = n;
+  for (int big = 0; big < 2 && a.k == 0; ++big) {
+    a.maxr = r_max_radix<T>(big);
+    a.k = r_radices(n, a.maxr, a.rad);
+  }
+  a.m = n;
+  if (a.k == 0) {
+    // Bluestein: among the lengths from 2n - 1 to a quarter more, the least values times
+    // stages
+    a.maxr = r_max_radix<T>(false);
+    double cost = 0;
+    for (int m = 2 * n - 1; m <= (5 * (2 * n - 1) + 3) / 4 + 8; ++m) {
+      int rad[kRMaxStages];
+      const int k = r_radices(m, a.maxr, rad);
+      if (k < 2 || (a.k && (double)m * k >= cost)) continue;
+      cost = (double)m * k;
+      a.m = m;
+      a.k = k;
+      for (int i = 0; i < k; ++i) a.rad[i] = rad[i];
+    }
+  }
+  if (a.k < 2) a.k = 0;
+  return a;
+}
+
+// Program of a pass of kind RL_*.
+inline void r_program(const RAxis& a, int kind, RProgram* p) {
+  const int k = a.k, *rad = a.rad;
+  const bool blue = a.blue();
+  p->n = a.n;
+  p->m = a.m;
+  p->steps = 0;
+  p->tw = p->chirp = p->filt = nullptr;
+  // transforms run one after the other, every second one with the radices reversed; the last
+  // stage of one and the first of the next are one step
+  const int nt = (blue ? 2 : 1) * (kind == RL_CONV ? 2 : 1);
+  for (int t = 0; t < nt; ++t) {
+    int L = 1;
+    for (int i = 0; i < k; ++i) {
+      const int r = t % 2 ? rad[k - 1 - i] : rad[i];
+      if (t == 0 || i > 0) {
+        RStep& s = p->st[p->steps++];
+        s.rad = (uint8_t)r;
+        s.nb = p->m / r;
+        s.L = L;
+        s.ts = p->m / (L * r);
+        const FDiv fn = fdiv_make((uint32_t)s.nb), fl = fdiv_make((uint32_t)L);
+        s.mnb = fn.m;
+        s.snb = (uint16_t)fn.s;
+        s.ml = fl.m;
+        s.sl = (uint16_t)fl.s;
+        s.in = RI_LDS;
+        s.op = RO_NONE;
+        s.out = RD_LDS;
+        if (t == 0 && i == 0)
+          s.in = blue ? (kind == RL_INV ? RI_BLUE_CONJ : RI_BLUE) : (kind == RL_INV ? RI_CONJ : RI_PLAIN);
+        if (i == k - 1 && t + 1 < nt)
+          s.op = !blue ? RO_PRODUCT : (t % 2 == 0 ? RO_FILTER : RO_BLUE_PRODUCT);
+        if (i == k - 1 && t + 1 == nt)
+          s.out = blue ? (kind == RL_FWD ? RD_BLUE : RD_BLUE_CONJ) : (kind == RL_FWD ? RD_PLAIN : RD_CONJ);
+      }
+      L *= r;
+    }
+  }
+}
+
+// ------------------------------------------------------------------ butterflies
+// cos and sin of 2 pi k / R at compile time (Taylor series on an eighth of a turn).
+template <int R>
+struct Roots {
+  double c[R], s[R];
+  static constexpr double taylor(double x, bool sine) {
+    double t = sine ? x : 1.0, acc = t;
+    for (int k = sine ? 1 : 0, i = 0; i < 14; ++i, k += 2) {
+      t = -t * x * x / ((k + 1) * (k + 2));
+      acc += t;
+    }
+    return acc;
+  }
+  constexpr Roots() : c(), s() {
+    constexpr double q = 0.78539816339744830962;  // pi/4
+    for (int k = 0; k < R; ++k) {
+      // 2 pi k / R = o pi/4 + x, |x| <= pi/8, with 8k = o R + rem
+      int o = 8 * k / R, rem = 8 * k - o * R;
+      if (2 * rem > R) {
+        ++o;
+        rem -= R;
+      }
+      const double x = q * rem / R, cx = taylor(x, false), sx = taylor(x, true);
+      constexpr double h = 0.70710678118654752440;
+      double a = cx, b = sx;  // rotated by o eighths
+      for (int i = 0; i < o % 2; ++i) {
+        const double t = h * (a - b);
+        b = h * (a + b);
+        a = t;
+      }
+      for (int i = 0; i < (o % 8) / 2; ++i) {
+        const double t = -b;
+        b = a;
+        a = t;
+      }
+      c[k] = a;
+      s[k] = b;
+    }
+  }
+};
+
+template <typename T, int R, bool INV>
+__device__ __forceinline__ void rdft(cpx<T>* x);
+
+// Odd prime P from the sums and differences of the pairs (s, P - s):
+// X_r, X_(P-r) = x_0 + sum_s a_s cos(2 pi r s/P) -+ i sum_s b_s sin(2 pi r s/P).
+template <typename T, int P, bool INV>
+__device__ __forceinline__ void rdft_prime(cpx<T>* x) {
+  constexpr int H = (P - 1) / 2;
+  constexpr Roots<P> W{};
+  cpx<T> a[H], b[H];
+  cpx<T> x0 = x[0];
+#pragma unroll
+  for (int s = 1; s <= H; ++s) {
+    a[s - 1] = x[s] + x[P - s];
+    b[s - 1] = x[s] - x[P - s];
+    x[0] = x[0] + a[s - 1];
+  }
+#pragma unroll
+  for (int r = 1; r <= H; ++r) {
+    cpx<T> C = x0, S = {0, 0};
+#pragma unroll
+    for (int s = 1; s <= H; ++s) {
+      const T c = (T)W.c[(r * s) % P], n = (T)W.s[(r * s) % P];
+      C = C + scl(a[s - 1], c);
+      S = S + scl(b[s - 1], n);
+    }
+    const cpx<T> iS = INV ? cpx<T>{S.im, -S.re} : cpx<T>{-S.im, S.re};  // +-i S
+    x[r] = C - iS;
+    x[P - r] = C + iS;
+  }
+}
+
+// R = R1 R2: with n = R2 n1 + n2 and k = k1 + R1 k2,
+// X_k = sum_n2 W_R2^(n2 k2) W_R^(n2 k1) sum_n1 W_R1^(n1 k1) x_n.
+template <typename T, int R1, int R2, bool INV>
+__device__ __forceinline__ void rdft_split(cpx<T>* x) {
+  constexpr int R = R1 * R2;
+  constexpr Roots<R> W{};
+  cpx<T> y[R2][R1];
+#pragma unroll
+  for (int n2 = 0; n2 < R2; ++n2) {
+#pragma unroll
+    for (int n1 = 0; n1 < R1; ++n1) y[n2][n1] = x[R2 * n1 + n2];
+    rdft<T, R1, INV>(y[n2]);
+#pragma unroll
+    for (int k1 = 1; k1 < R1; ++k1)
+      if (n2 > 0)
+        y[n2][k1] = y[n2][k1] * cpx<T>{(T)W.c[n2 * k1], INV ? (T)W.s[n2 * k1] : (T)-W.s[n2 * k1]};
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < R1; ++k1) {
+    cpx<T> b[R2];
+#pragma unroll
+    for (int n2 = 0; n2 < R2; ++n2) b[n2] = y[n2][k1];
+    rdft<T, R2, INV>(b);
+#pragma unroll
+    for (int k2 = 0; k2 < R2; ++k2) x[k1 + R1 * k2] = b[k2];
+  }
+}
+
+template <typename T, int R, bool INV>
+__device__ __forceinline__ void rdft(cpx<T>* x) {
+  if constexpr (R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 16) dft<T, R, INV>(x);
+  else if constexpr (R == 6) rdft_split<T, 3, 2, INV>(x);
+  else if constexpr (R == 9) rdft_split<T, 3, 3, INV>(x);
+  else if constexpr (R == 10) rdft_split<T, 5, 2, INV>(x);
+  else if constexpr (R == 12) rdft_split<T, 4, 3, INV>(x);
+  else if constexpr (R == 14) rdft_split<T, 7, 2, INV>(x);
+  else if constexpr (R == 15) rdft_split<T, 5, 3, INV>(x);
+  else rdft_prime<T, R, INV>(x);
+}
+
+// Butterflies of radix R that a thread holds at once: 10 values, 20 in the strided FP32 tiles
+// (whose 16 columns would otherwise need more than a block of threads).
+template <typename T, bool STRIDED>
+__host__ __device__ constexpr int r_batch(int R) {
+  const int q = (sizeof(T) == 4 && STRIDED ? 20 : 10) / R;
+  return q < 1 ? 1 : q > 4 ? 4 : q;
+}
+
+// Threads for nl lines of an axis: every stage in one batch; a power of two, so that a
+// block's waves load the four SIMDs of a CU alike.
+template <typename T>
+inline int r_threads(const RAxis& a, int nl, bool strided) {
+  int t = 64;
+  for (int s = 0; s < a.k; ++s) {
+    const int q = strided ? r_batch<T, true>(a.rad[s]) : r_batch<T, false>(a.rad[s]);
+    const int need = (nl * (a.m / a.rad[s]) + q - 1) / q;
+    while (t < need) t *= 2;
+  }
+  return t;
+}
+
+// Lines of a tile in LDS.  NLC > 0: NLC lines, the line index fastest (strided lines: a
+// global run of NLC values is an LDS run); NLC = 0: lines apart, one spare value every 8 (the
+// butterflies of neighbouring threads write 8 apart).
+template <int NLC>
+struct RTile {
+  int nl;  // lines (NLC = 0)
+  int ls;  // LDS values of a line (NLC = 0)
+  __device__ __forceinline__ int lines() const { return NLC > 0 ? NLC : nl; }
+  __device__ __forceinline__ int at(int l, int e) const {
+    return NLC > 0 ? e * NLC + l : l * ls + e + (e >> 3);
+  }
+  // butterfly u of a stage with nb butterflies a line -> (line, butterfly)
+  __device__ __forceinline__ void locate(int u, FDiv fnb, int nb, int* l, int* t) const {
+    if constexpr (NLC > 0) {
+      *l = u % NLC;
+      *t = u / NLC;
+    } else {
+      *l = (int)fdiv((uint32_t)u, fnb);
+      *t = u - *l * nb;
+    }
+  }
+};
+__host__ __device__ constexpr int r_line_slots(int n) { return n + (n >> 3) + 1; }
+
+// One step with radix R: butterfly t of line l takes the elements t + k nb, twiddled by
+// W_(L R)^(k j), j = t mod L, and leaves the elements (t - j) R + j + k L.  load(l, e),
+// product(l, e, v) and store(l, e, v) are the caller's, as is first(), which the first step
+// calls once its loads are under way.
+template <typename T, int R, int NLC, typename Load, typename Product, typename Store,
+          typename First>
+__device__ __forceinline__ void r_step(const RTile<NLC>& tile, const RProgram* __restrict__ p,
+                                       const RStep& st, const cpx<T>* tw, cpx<T>* buf, Load load,
+                                       Product product, Store store, First first) {
+  constexpr int Q = r_batch<T, (NLC > 0)>(R);
+  const cpx<T>* __restrict__ ch = reinterpret_cast<const cpx<T>*>(p->chirp);
+  const int n = p->n, nb = st.nb, L = st.L, tot = tile.lines() * nb;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  cpx<T> v[Q][R];
+  int ll[Q], tt[Q], jj[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int u = tid + q * nt;
+    if (u < tot) {
+      int l, t;
+      tile.locate(u, st.fnb(), nb, &l, &t);
+      ll[q] = l;
+      tt[q] = t;
+      const int j = t - (int)fdiv((uint32_t)t, st.fl()) * L;
+      jj[q] = j;
+      if (st.in == RI_LDS) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[q][k] = buf[tile.at(l, t + k * nb)];
+#pragma unroll
+        for (int k = 1; k < R; ++k) v[q][k] = v[q][k] * tw[k * j * st.ts];
+      } else if (st.in <= RI_CONJ) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[q][k] = load(l, t + k * nb);
+        if (st.in == RI_CONJ) {
+#pragma unroll
+          for (int k = 0; k < R; ++k) v[q][k].im = -v[q][k].im;
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const int e = t + k * nb, ec = min(e, n - 1);
+          cpx<T> x = load(l, ec);
+          if (st.in == RI_BLUE_CONJ) x.im = -x.im;
+          x = x * ch[ec];
+          v[q][k] = cpx<T>{e < n ? x.re : (T)0, e < n ? x.im : (T)0};
+        }
+      }
+      rdft<T, R, false>(v[q]);
+      if (st.op != RO_NONE) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const int e = t + k * nb;
+          cpx<T> x = v[q][k];
+          if (st.op == RO_PRODUCT) {
+            x = product(l, e, x);
+          } else if (st.op == RO_FILTER) {
+            x = x * reinterpret_cast<const cpx<T>*>(p->filt)[e];
+          } else {
+            const int ec = min(e, n - 1);
+            const cpx<T> c = ch[ec];
+            x.im = -x.im;
+            x = product(l, ec, x * c);
+            // conj(x) c, conjugated once more below with the others
+            x = x * conjg(c);
+            x = cpx<T>{e < n ? x.re : (T)0, e < n ? x.im : (T)0};
+          }
+          v[q][k] = conjg(x);
+        }
+        rdft<T, R, false>(v[q]);
+      }
+    }
+  }
+  if (st.in != RI_LDS) first();
+  if (st.out == RD_LDS) {
+    if (st.in == RI_LDS) __syncthreads();  // every operand is read
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (tid + q * nt < tot) {
+        const int o = st.op != RO_NONE ? tt[q] * R : (tt[q] - jj[q]) * R + jj[q];
+        const int d = st.op != RO_NONE ? 1 : L;
+#pragma unroll
+        for (int k = 0; k < R; ++k) buf[tile.at(ll[q], o + k * d)] = v[q][k];
+      }
+    }
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (tid + q * nt < tot) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          const int e = tt[q] + k * nb;  // the last stage: L = nb, j = t
+          cpx<T> x = v[q][k];
+          if (st.out <= RD_CONJ) {
+            if (st.out == RD_CONJ) x.im = -x.im;
+            store(ll[q], e, x);
+          } else if (e < n) {
+            x = conjg(x) * ch[e];
+            if (st.out == RD_BLUE_CONJ) x.im = -x.im;
+            store(ll[q], e, x);
+          }
+        }
+      }
+    }
+  }
+}
+
+// The program of a tile's lines.  tw: its twiddles in LDS (the first step reads none, so
+// first() may write them); buf: LDS of the tile, free.
+template <typename T, int MAXR, int NLC, typename Load, typename Product, typename Store,
+          typename First>
+__device__ __forceinline__ void r_run(const RTile<NLC>& tile, const RProgram* __restrict__ p,
+                                      const cpx<T>* tw, cpx<T>* buf, Load load, Product product,
+                                      Store store, First first) {
+  const int steps = p->steps;
+  for (int s = 0; s < steps; ++s) {
+    const RStep st = p->st[s];
+    switch (st.rad) {
+#define GP_R(R)                                                      \
+  case R:                                                            \
+    if constexpr (R <= MAXR) r_step<T, R>(tile, p, st, tw, buf, load, product, store, first); \
+    break;
+      GP_R(2) GP_R(3) GP_R(4) GP_R(5) GP_R(6) GP_R(7) GP_R(8) GP_R(9) GP_R(10) GP_R(11) GP_R(12)
+      GP_R(13) GP_R(14) GP_R(15) GP_R(16)
+#undef GP_R
+      default:
+        break;
+    }
+  }
+}
+
+// ------------------------------------------------------------------- line passes
+// Lines of the half spectrum.  NLC > 0: lines at stride `es` (elements), NLC adjacent columns
+// of one plane to a tile (`cols` columns to a plane, plane stride `ps`); NLC = 0: contiguous
+// lines, nl to a tile, at LDS stride ls.
+struct RLines {
+  int nlines, nl, ls;
+  int cols;
+  unsigned es;
+  long long ps;
+};
+
+// A copy from global memory to LDS whose loads are issued at once (NU values per thread) and
+// whose stores come later.
+template <typename X, int NU>
+struct Prefetch {
+  X v[NU];
+  template <typename F>
+  __device__ __forceinline__ void load(int n, F f) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int t = threadIdx.x + u * blockDim.x;
+      v[u] = f(t < n ? t : 0);
+    }
+  }
+  template <typename F>
+  __device__ __forceinline__ void store(int n, X* dst, F f) {
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int t = threadIdx.x + u * blockDim.x;
+      if (t < n) dst[t] = v[u];
+    }
+    for (int t = threadIdx.x + NU * blockDim.x; t < n; t += blockDim.x) dst[t] = f(t);
+  }
+};
+
+// Kernel value of element e of line l of a convolution: 3D (strided) the quadrant
+// ktab[(kx (n2/2+1) + min(e, n2-e)) (n1/2+1) + min(k1, n1-k1)] of line l = kx n1 + k1, 2D
+// ktab[l n + e]; a tile's values wait in LDS for the product.  The product is
+// U(k) scale^2 / N (the table holds U/N).
+template <typename T, int NLC, int MAXR>
+__global__ void __launch_bounds__(kRThreads) k_rlines(cpx<T>* __restrict__ data, RLines g,
+                                                      const RProgram* __restrict__ p,
+                                                      const T* __restrict__ ktab,
+                                                      const double* __restrict__ scale) {
+  constexpr unsigned CB = sizeof(cpx<T>);
+  extern __shared__ __align__(16) char rfft_raw[];
+  const int n = p->n, m = p->m;
+  const RTile<NLC> tile{g.nl, g.ls};
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(rfft_raw);
+  cpx<T>* buf = tw + m;
+  T* kt = reinterpret_cast<T*>(buf + (NLC > 0 ? m * NLC : g.nl * g.ls));
+  // tiles numbered XCD-contiguously: neighbours share 128-byte lines and an L2
+  const int b = xcd_tile(blockIdx.x, gridDim.x);
+  int plane = 0, l0;
+  cpx<T>* base;
+  unsigned bytes, step;
+  if constexpr (NLC > 0) {
+    const int tiles = (g.cols + NLC - 1) / NLC;
+    plane = b / tiles;
+    l0 = (b - plane * tiles) * NLC;
+    base = data + (plane * g.ps + l0);
+    step = g.es * CB;
+    bytes = (unsigned)(n - 1) * step + (unsigned)min(NLC, g.cols - l0) * CB;
+  } else {
+    l0 = b * g.nl;
+    base = data + (long long)l0 * n;
+    step = CB;
+    bytes = (unsigned)min(g.nl, g.nlines - l0) * (unsigned)n * CB;
+  }
+  const __amdgpu_buffer_rsrc_t rb = buf_of(base, bytes);
+  // lines past the grid: out of the buffer's range (strided lines start past it)
+  auto off = [&](int l, int e) -> unsigned {
+    if constexpr (NLC > 0)
+      return (l0 + l < g.cols ? (unsigned)l * CB : bytes) + (unsigned)e * step;
+    else
+      return ((unsigned)l * (unsigned)n + (unsigned)e) * CB;
+  };
+  // the tables are fetched ahead of the first step's operands and kept after it
+  const cpx<T>* __restrict__ twg = reinterpret_cast<const cpx<T>*>(p->tw);
+  auto tw_of = [&](int t) { return twg[t]; };
+  const int nk = ktab == nullptr ? 0 : NLC > 0 ? (n / 2 + 1) * NLC : min(g.nl, g.nlines - l0) * n;
+  auto kt_of = [&](int t) {
+    if constexpr (NLC > 0) {
+      const int k1 = min(l0 + t % NLC, g.cols - 1), h1 = g.cols / 2 + 1;
+      return at32(ktab + (size_t)plane * (n / 2 + 1) * h1,
+                  (unsigned)(t / NLC * h1 + min(k1, g.cols - k1)));
+    } else {
+      return at32(ktab + (size_t)l0 * n, (unsigned)t);
+    }
+  };
+  Prefetch<cpx<T>, 1> ptw;
+  Prefetch<T, 4> pkt;
+  ptw.load(m, tw_of);
+  T s2 = 1;
+  if (nk > 0) {
+    pkt.load(nk, kt_of);
+    const double sc = *scale;
+    s2 = (T)(sc * sc);
+  }
+  r_run<T, MAXR>(
+      tile, p, tw, buf,
+      [&](int l, int e) {
+        cpx<T> v;
+        buf_load(rb, off(l, e), v);
+        return v;
+      },
+      [&](int l, int e, cpx<T> v) {
+        T k;
+        if constexpr (NLC > 0) k = kt[min(e, n - e) * NLC + l];
+        else k = kt[min(l, g.nlines - 1 - l0) * n + e];
+        return scl(v, k * s2);
+      },
+      [&](int l, int e, cpx<T> v) { buf_store(rb, off(l, e), v); },
+      [&] {
+        ptw.store(m, tw, tw_of);
+        if (nk > 0) pkt.store(nk, kt, kt_of);
+      });
+}
+
+// Keeps a program in device memory.
+__global__ inline void k_rprogram(RProgram p, RProgram* __restrict__ dst) {
+  static_assert(sizeof(RProgram) % 4 == 0, "copied by words");
+  const int* s = reinterpret_cast<const int*>(&p);
+  int* d = reinterpret_cast<int*>(dst);
+  for (int i = threadIdx.x; i < (int)(sizeof(RProgram) / 4); i += blockDim.x) d[i] = s[i];
+}
+
+}  // namespace gpdbec

@@ -1,0 +1,47 @@
+// Host side of the run-time-length FFT passes (gp_rfft.hpp), one instantiation per precision
+// in gp_rfft_inst.hip.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+
+#include "gp_rfft.hpp"
+
+namespace gpdbec {
+
+// LDS a block may take (of 160 KiB per CU).
+constexpr size_t kRLds = 143360;
+
+template <typename T>
+struct RLaunch {
+  // raises the kernels' dynamic LDS limit (once per process, outside any capture)
+  static hipError_t prepare();
+  // keeps the program of a pass in device memory (tables: twiddles, chirp, filter)
+  static hipError_t program(hipStream_t st, const RAxis& a, int kind, const void* tw,
+                            const void* chirp, const void* filt, RProgram* dst);
+  // whether an axis's lines have these passes, contiguous or strided
+  static bool contiguous_ok(const RAxis& a);
+  static bool strided_ok(const RAxis& a, int cols);
+  // contiguous lines of a.n points (nlines of them); scale, ktab: the convolution's
+  static hipError_t contiguous(hipStream_t st, cpx<T>* data, int nlines, const RAxis& a,
+                               const RProgram* p, const T* ktab, const double* scale);
+  // lines at stride cols in `planes` planes of a.n x cols values (convolution: the 3D
+  // quadrant table)
+  static hipError_t strided(hipStream_t st, cpx<T>* data, int cols, int planes, const RAxis& a,
+                            const RProgram* p, const T* ktab, const double* scale);
+};
+
+#define GP_DECLARE_RFFT(T)                                                                     \
+  template <> hipError_t RLaunch<T>::prepare();                                                \
+  template <> hipError_t RLaunch<T>::program(hipStream_t, const RAxis&, int, const void*,      \
+                                             const void*, const void*, RProgram*);             \
+  template <> bool RLaunch<T>::contiguous_ok(const RAxis&);                                    \
+  template <> bool RLaunch<T>::strided_ok(const RAxis&, int);                                  \
+  template <> hipError_t RLaunch<T>::contiguous(hipStream_t, cpx<T>*, int, const RAxis&,       \
+                                                const RProgram*, const T*, const double*);     \
+  template <> hipError_t RLaunch<T>::strided(hipStream_t, cpx<T>*, int, int, const RAxis&,     \
+                                             const RProgram*, const T*, const double*);
+GP_DECLARE_RFFT(float)
+GP_DECLARE_RFFT(double)
+#undef GP_DECLARE_RFFT
+
+}  // namespace gpdbec

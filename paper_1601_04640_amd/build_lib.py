@@ -46,10 +46,12 @@ def _jobs(build_dir=BUILD, extra=()):
                            f"-DGP_SWEEP_FP32={int(real == 'float')}", "-c",
                            os.path.join(CSRC, "gp_sweep_inst.hip"), "-o", obj]))
     for real in ("float", "double"):
-        obj = os.path.join(build_dir, f"rfft_{real}.o")
-        jobs.insert(0, (obj, [HIPCC, *FLAGS, *extra, f"-DGP_REAL={real}",
-                              f"-DGP_RFFT_FP32={int(real == 'float')}", "-c",
-                              os.path.join(CSRC, "gp_rfft_inst.hip"), "-o", obj]))
+        for fam in (0, 1):
+            obj = os.path.join(build_dir, f"rfft_{real}_{fam}.o")
+            jobs.insert(0, (obj, [HIPCC, *FLAGS, *extra, f"-DGP_REAL={real}",
+                                  f"-DGP_RFFT_FP32={int(real == 'float')}",
+                                  f"-DGP_FAMILY={fam}", "-c",
+                                  os.path.join(CSRC, "gp_rfft_inst.hip"), "-o", obj]))
     obj = os.path.join(build_dir, "capi.o")
     jobs.append((obj, [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, "gp_capi.hip"), "-o", obj]))
     # host-only code over the public C ABI (saved states, output cadence)

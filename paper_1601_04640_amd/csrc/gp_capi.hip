@@ -88,6 +88,7 @@ struct Layout {
   // FFT passes of run-time-length axes with the data in registers between stages
   // (gp_rfft.hpp); k = 0: the other kernels
   RAxis ra[3];
+  RXCfg xr, xc;  // the x passes of such an x axis
   // the y and z sweeps (axes 1, 2) over strided columns; S = 0: another form
   SweepCfg sw[3];
   GLong lg[2];
@@ -191,6 +192,13 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
   L.sy = L.sy || L.ly;
   // y lines are contiguous in the spectrum, z lines strided (no long axis: those split)
   if (L.generic && !L.lx && !L.ly) {
+    const RAxis a0 = fp64 ? r_axis<double>(L.n0) : r_axis<float>(L.n0);
+    L.xr = fp64 ? RLaunch<double>::x_r2c(a0, L.n1, L.n2) : RLaunch<float>::x_r2c(a0, L.n1, L.n2);
+    L.xc = fp64 ? RLaunch<double>::x_c2r(a0, L.n1, L.n2) : RLaunch<float>::x_c2r(a0, L.n1, L.n2);
+    if (L.xr.blocks && L.xc.blocks) {
+      L.ra[0] = a0;
+      L.sw[0] = L.xc.sweep();
+    }
     RAxis a1 = fp64 ? r_axis<double>(L.n1) : r_axis<float>(L.n1);
     if (fp64 ? RLaunch<double>::contiguous_ok(a1) : RLaunch<float>::contiguous_ok(a1)) L.ra[1] = a1;
     if (p->geom == GP_3D) {
@@ -218,6 +226,10 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
     L.nb_r2c = L.nb_x;
     L.nb_nl = fp64 ? GLaunch<double>::nl_blocks(L.n0, L.n1, L.n2)
                    : GLaunch<float>::nl_blocks(L.n0, L.n1, L.n2);
+    if (L.ra[0].k) {
+      L.nb_x = L.nb_r2c = L.xr.blocks;
+      L.nb_nl = L.xc.blocks;
+    }
     // blocks of the last sweep (z in 3D, y in 2D), which the z observe shares
     const int last = p->geom == GP_3D ? 2 : 1;
     L.nb_col = L.sw[last].S ? L.sw[last].blocks
@@ -561,6 +573,10 @@ struct Passes {
               GLaunch<T>::lx_r2c(c->st, src, gscr(c), spec(c), L.lxg, c->lplan[0][0],
                                  c->lplan[0][1], ltw(c, 0, 0), ltw(c, 0, 1), ltw(c, 0, 2),
                                  c->at<double>(L.o_px[0])));
+    } else if (L.ra[0].k) {
+      GP_PASS(c, GP_PASS_R2C_X,
+              RLaunch<T>::r2c(c->st, L.xr, L.ra[0], src, spec(c), rprog(c, 0, RL_FWD),
+                              c->at<double>(L.o_px[0])));
     } else {
       GP_PASS(c, GP_PASS_R2C_X,
               GLaunch<T>::r2c_x(c->st, src, spec(c), c->gplan[0], tw(c, 0),
@@ -603,12 +619,26 @@ struct Passes {
                  fdiv_make((uint32_t)c->L.n0), fdiv_make((uint32_t)c->L.n1)};
   }
 
+  // the fused complex-to-real pass: psi, V, scale, the x sweep's tables (factor set k), sums
+  static RXArgs<T> g_xargs(gp_ctx* c, int k) {
+    const Layout& L = c->L;
+    return RXArgs<T>{psi(c), Vp(c), &c->sc()->scale, cn(c, 0, k), c->at<cpx<T>>(L.o_sw[0][k]),
+                     c->p.dt, c->gc, c->p.gdd, L.h0, L.h1, L.h2, c->at<double>(L.o_pnl), nullptr};
+  }
+
   // the x C2R of the convolved spectrum into phi
   static gp_status g_c2r(gp_ctx* c, T* phi) {
     const Layout& L = c->L;
     if (L.lx)
       return dev(GLaunch<T>::lx_c2r(c->st, spec(c), gscr(c), phi, L.lxg, c->lplan[0][0],
                                     c->lplan[0][1], ltw(c, 0, 0), ltw(c, 0, 1), ltw(c, 0, 2)));
+    if (L.ra[0].k) {
+      RXArgs<T> g = g_xargs(c, 0);
+      g.part = nullptr;
+      g.phi = phi;
+      return dev(RLaunch<T>::c2r(c->st, L.xc, L.ra[0], MODE_OBSERVE, spec(c), rprog(c, 0, RL_INV),
+                                 g));
+    }
     return dev(GLaunch<T>::c2r_x(c->st, spec(c), phi, c->gplan[0], tw(c, 0), L.n0, L.n1, L.n2));
   }
 
@@ -626,7 +656,7 @@ struct Passes {
     const cpx<T>* f = mode == 2 ? nullptr : cn(c, axis, k);
     const long long plane = (long long)L.n0 * L.n1;
     cpx<T>* dscr = c->at<cpx<T>>(L.o_gscr);
-    if (L.sw[axis].S) {  // y or z over the strided columns (2D: one outer index)
+    if (axis > 0 && L.sw[axis].S) {  // y or z over the strided columns (2D: one outer index)
       const int n = axis == 1 ? L.n1 : L.n2;
       return dev(SweepLaunch<T>::run(L.sw[axis], mode, k != 0, c->st, psi(c), f,
                                      c->at<cpx<T>>(L.o_sw[axis][k]), pc, n, L.n0,
@@ -666,8 +696,11 @@ struct Passes {
     GP_TRY(settle(c));
     GP_TRY(g_convolution(c, psi(c), &c->sc()->scale));
     GP_TRY(pass_begin(c, GP_PASS_C2R_NL_CNX));
-    GP_TRY(g_c2r(c, phi));
-    if (L.lx) {
+    if (!L.ra[0].k) GP_TRY(g_c2r(c, phi));
+    if (L.ra[0].k) {
+      GP_HIP(RLaunch<T>::c2r(c->st, L.xc, L.ra[0], mode, spec(c), rprog(c, 0, RL_INV),
+                             g_xargs(c, k)));
+    } else if (L.lx) {
       // long x lines: the nonlinear sub-step in place, then the segmented sweep
       GP_HIP(GLaunch<T>::nonlinear(mode, c->st, psi(c), Vp(c), phi, &c->sc()->scale,
                                    g_scalars(c), L.n0, L.n1, L.n2, c->at<double>(L.o_pnl)));
@@ -698,6 +731,13 @@ struct Passes {
   static gp_status g_observe(gp_ctx* c) {
     const Layout& L = c->L;
     T* phi = c->at<T>(L.o_sfield);
+    if (L.ra[0].k) {
+      GP_TRY(g_convolution(c, psi(c), &c->sc()->scale));
+      GP_HIP(RLaunch<T>::c2r(c->st, L.xc, L.ra[0], MODE_OBSERVE, spec(c), rprog(c, 0, RL_INV),
+                             g_xargs(c, 0)));
+      if (c->p.geom == GP_3D) return z_observe(c, FIN_OBSERVE);
+      return finalize(c, FIN_OBSERVE);
+    }
     GP_TRY(g_phi(c, psi(c), &c->sc()->scale, phi));
     GP_HIP(GLaunch<T>::nonlinear(MODE_OBSERVE, c->st, psi(c), Vp(c), phi,
                                  &c->sc()->scale, g_scalars(c), L.n0, L.n1, L.n2,

@@ -22,7 +22,9 @@ namespace gpdbec {
 
 constexpr int kRMaxStages = 6;
 constexpr int kRMaxRadix = 16;
-constexpr int kRThreads = 512;  // largest block
+// Largest block: FP32 kernels take at most 128 VGPRs.
+template <typename T>
+constexpr int r_max_threads() { return sizeof(T) == 4 ? 1024 : 512; }
 
 // What a step reads, does to its butterflies' results, and writes.  Every transform runs
 // forward: an inverse one is the conjugate of the forward transform of the conjugate, taken
@@ -313,6 +315,18 @@ inline int r_threads(const RAxis& a, int nl, bool strided) {
   return t;
 }
 
+// Threads of a pass of few blocks: doubled while the GPU has room (two waves per SIMD, one
+// on a CU's every SIMD for each of 256 blocks) and a stage has a butterfly for each, so that
+// a wave issues fewer instructions one after the other.
+template <typename T>
+inline int r_spread(const RAxis& a, int nl, int threads, long long blocks) {
+  int wide = 0;
+  for (int s = 0; s < a.k; ++s) wide = nl * (a.m / a.rad[s]) > wide ? nl * (a.m / a.rad[s]) : wide;
+  while (threads < wide && 2 * threads <= r_max_threads<T>() && 2 * threads * blocks <= 256 * 1024)
+    threads *= 2;
+  return threads;
+}
+
 // Lines of a tile in LDS.  NLC > 0: NLC lines, the line index fastest (strided lines: a
 // global run of NLC values is an LDS run); NLC = 0: lines apart, one spare value every 8 (the
 // butterflies of neighbouring threads write 8 apart).
@@ -341,8 +355,10 @@ __host__ __device__ constexpr int r_line_slots(int n) { return n + (n >> 3) + 1;
 // W_(L R)^(k j), j = t mod L, and leaves the elements (t - j) R + j + k L.  load(l, e),
 // product(l, e, v) and store(l, e, v) are the caller's, as is first(), which the first step
 // calls once its loads are under way.
-template <typename T, int R, int NLC, typename Load, typename Product, typename Store,
-          typename First>
+// ALIAS: load and store work on buf itself (the last step leaves its results where its
+// operands were, so only the first one needs a barrier more).
+template <typename T, int R, bool ALIAS, int NLC, typename Load, typename Product,
+          typename Store, typename First>
 __device__ __forceinline__ void r_step(const RTile<NLC>& tile, const RProgram* __restrict__ p,
                                        const RStep& st, const cpx<T>* tw, cpx<T>* buf, Load load,
                                        Product product, Store store, First first) {
@@ -411,7 +427,7 @@ __device__ __forceinline__ void r_step(const RTile<NLC>& tile, const RProgram* _
   }
   if (st.in != RI_LDS) first();
   if (st.out == RD_LDS) {
-    if (st.in == RI_LDS) __syncthreads();  // every operand is read
+    if (ALIAS || st.in == RI_LDS) __syncthreads();  // every operand is read
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       if (tid + q * nt < tot) {
@@ -446,18 +462,20 @@ __device__ __forceinline__ void r_step(const RTile<NLC>& tile, const RProgram* _
 
 // The program of a tile's lines.  tw: its twiddles in LDS (the first step reads none, so
 // first() may write them); buf: LDS of the tile, free.
-template <typename T, int MAXR, int NLC, typename Load, typename Product, typename Store,
-          typename First>
+template <typename T, int MAXR, bool ALIAS, int NLC, typename Load, typename Product,
+          typename Store, typename First>
 __device__ __forceinline__ void r_run(const RTile<NLC>& tile, const RProgram* __restrict__ p,
                                       const cpx<T>* tw, cpx<T>* buf, Load load, Product product,
                                       Store store, First first) {
   const int steps = p->steps;
+  RStep next = p->st[0];
   for (int s = 0; s < steps; ++s) {
-    const RStep st = p->st[s];
+    const RStep st = next;
+    next = p->st[min(s + 1, steps - 1)];  // read a step ahead
     switch (st.rad) {
 #define GP_R(R)                                                      \
   case R:                                                            \
-    if constexpr (R <= MAXR) r_step<T, R>(tile, p, st, tw, buf, load, product, store, first); \
+    if constexpr (R <= MAXR) r_step<T, R, ALIAS>(tile, p, st, tw, buf, load, product, store, first); \
     break;
       GP_R(2) GP_R(3) GP_R(4) GP_R(5) GP_R(6) GP_R(7) GP_R(8) GP_R(9) GP_R(10) GP_R(11) GP_R(12)
       GP_R(13) GP_R(14) GP_R(15) GP_R(16)
@@ -508,7 +526,7 @@ struct Prefetch {
 // ktab[l n + e]; a tile's values wait in LDS for the product.  The product is
 // U(k) scale^2 / N (the table holds U/N).
 template <typename T, int NLC, int MAXR>
-__global__ void __launch_bounds__(kRThreads) k_rlines(cpx<T>* __restrict__ data, RLines g,
+__global__ void __launch_bounds__(r_max_threads<T>()) k_rlines(cpx<T>* __restrict__ data, RLines g,
                                                       const RProgram* __restrict__ p,
                                                       const T* __restrict__ ktab,
                                                       const double* __restrict__ scale) {
@@ -567,7 +585,7 @@ __global__ void __launch_bounds__(kRThreads) k_rlines(cpx<T>* __restrict__ data,
     const double sc = *scale;
     s2 = (T)(sc * sc);
   }
-  r_run<T, MAXR>(
+  r_run<T, MAXR, false>(
       tile, p, tw, buf,
       [&](int l, int e) {
         cpx<T> v;

@@ -1,4 +1,5 @@
-// Instantiations of the run-time-length FFT passes for one precision (GP_REAL).
+// Instantiations of the run-time-length FFT passes for one precision (GP_REAL) and family:
+//   GP_FAMILY 0: line passes and programs    1: x passes
 #include <mutex>
 
 #include "gp_rfft_launch.hpp"
@@ -10,10 +11,16 @@
 namespace gpdbec {
 using T = GP_REAL;
 
+#if GP_FAMILY == 0
+hipError_t rx_prepare(T);  // the x passes' LDS limits (family 1)
+#endif
+
 namespace {
 constexpr bool F32 = sizeof(T) == 4;
 constexpr int kSmall = r_max_radix<T>(false), kBig = r_max_radix<T>(true);
+constexpr int kWide = F32 ? 16 : 8;   // lines of a tile side by side: 128-byte runs
 
+#if GP_FAMILY == 0
 // every (lines per tile, largest radix) instantiated
 #if GP_RFFT_FP32
 #define GP_FOR_RLINES(X) X(0, kSmall) X(16, kSmall) X(8, kSmall) X(4, kSmall)
@@ -21,7 +28,6 @@ constexpr int kSmall = r_max_radix<T>(false), kBig = r_max_radix<T>(true);
 #define GP_FOR_RLINES(X) \
   X(0, kSmall) X(8, kSmall) X(4, kSmall) X(2, kSmall) X(0, kBig) X(8, kBig) X(4, kBig) X(2, kBig)
 #endif
-constexpr int kWide = F32 ? 16 : 8;   // columns of a strided tile: 128-byte runs
 constexpr int kNarrow = F32 ? 4 : 2;
 
 // LDS: the twiddles, the lines and the tile's kernel values
@@ -33,7 +39,7 @@ size_t lds_contiguous(const RAxis& a, int nl, bool conv) {
          (conv ? sizeof(T) * (size_t)nl * a.n : 0);
 }
 bool fits(const RAxis& a, int nl, size_t lds, bool strided) {
-  return a.k > 0 && lds <= kRLds && r_threads<T>(a, nl, strided) <= kRThreads;
+  return a.k > 0 && lds <= kRLds && r_threads<T>(a, nl, strided) <= r_max_threads<T>();
 }
 
 // Columns of a strided tile: 128-byte runs while the tile's lines leave room for two blocks
@@ -72,6 +78,8 @@ hipError_t RLaunch<T>::prepare() {
         hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRLds);
     if (e != hipSuccess) return e;
   }
+  const hipError_t e = rx_prepare(T{});
+  if (e != hipSuccess) return e;
   done = true;
   return hipSuccess;
 }
@@ -120,7 +128,8 @@ hipError_t RLaunch<T>::contiguous(hipStream_t st, cpx<T>* data, int nlines, cons
   if (!contiguous_ok(a) || nlines < 1) return hipErrorInvalidValue;
   const int nl = contiguous_lines(a, nlines);
   const RLines g{nlines, nl, r_line_slots(a.m), 0, 1u, 0};
-  return launch<0>(st, (nlines + nl - 1) / nl, r_threads<T>(a, nl, false),
+  const int blocks = (nlines + nl - 1) / nl;
+  return launch<0>(st, blocks, r_spread<T>(a, nl, r_threads<T>(a, nl, false), blocks),
                    lds_contiguous(a, nl, ktab != nullptr), data,
                    g, a.maxr, p, ktab, scale);
 }
@@ -133,7 +142,8 @@ hipError_t RLaunch<T>::strided(hipStream_t st, cpx<T>* data, int cols, int plane
   // few tiles: half the columns (FP32 75x63 planes: 9.1 us, 8.4 with half)
   if (c == kWide && (long long)((cols + c - 1) / c) * planes < 512) c /= 2;
   const RLines g{cols * planes, c, 0, cols, (unsigned)cols, (long long)cols * a.n};
-  const int blocks = (cols + c - 1) / c * planes, th = r_threads<T>(a, c, true);
+  const int blocks = (cols + c - 1) / c * planes;
+  const int th = r_spread<T>(a, c, r_threads<T>(a, c, true), blocks);
   const size_t lds = lds_strided(a, c);
   switch (c) {
 #if GP_RFFT_FP32
@@ -146,5 +156,144 @@ hipError_t RLaunch<T>::strided(hipStream_t st, cpx<T>* data, int cols, int plane
     default: return hipErrorInvalidValue;
   }
 }
+
+#else  // x passes
+}  // namespace
+
+hipError_t rx_prepare(T) {
+  const void* ks[] = {
+#define X(M)                                                       \
+  reinterpret_cast<const void*>(&k_rr2c<T, M>),                    \
+      reinterpret_cast<const void*>(&k_rc2r<T, M, MODE_IMAG, 8>),  \
+      reinterpret_cast<const void*>(&k_rc2r<T, M, MODE_REAL, 8>),  \
+      reinterpret_cast<const void*>(&k_rc2r<T, M, MODE_OBSERVE, 8>)
+      X(kSmall),
+#if GP_RFFT_FP32
+      reinterpret_cast<const void*>(&k_rc2r<T, kSmall, MODE_IMAG, 16>),
+      reinterpret_cast<const void*>(&k_rc2r<T, kSmall, MODE_REAL, 16>),
+#else
+      X(kBig),
+#endif
+#undef X
+  };
+  for (const void* k : ks) {
+    const hipError_t e =
+        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRLds);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+namespace {
+// The tile of an x pass: the most line pairs (runs of up to 128 bytes along the spectrum's y)
+// that leave room for two blocks on a CU and the grid 256 blocks, else one pair.
+template <typename F>
+RXCfg x_shape(const RAxis& a, int n1, int n2, F size) {
+  RXCfg best;
+  if (a.k < 2 || (double)a.n * (kWide + 1) * sizeof(cpx<T>) >= 2147483648.0) return best;
+  const int pairs = (n1 + 1) / 2;
+  for (int np = kWide / 2; np >= 1; np /= 2) {
+    if (np > 1 && np / 2 >= pairs) continue;
+    RXCfg c;
+    c.xt.n0 = a.n;
+    c.xt.n1 = n1;
+    c.xt.n2 = n2;
+    c.xt.np = np;
+    c.xt.nbj = (pairs + np - 1) / np;
+    c.xt.ls = r_line_slots(a.m) | 1;
+    c.xt.fn0 = fdiv_make((uint32_t)a.n);
+    c.xt.fnp = fdiv_make((uint32_t)np);
+    const double blocks = (double)c.xt.nbj * n2;
+    size(c);
+    if (c.threads > r_max_threads<T>() || c.lds > kRLds || blocks > 2147483647.0) continue;
+    c.blocks = c.xt.nbj * n2;
+    // (where one block fills a CU's LDS anyway, the longer runs)
+    if (best.blocks == 0 || c.lds <= 81920) best = c;
+    if (c.lds <= 81920 && blocks >= 256) break;
+  }
+  return best;
+}
+}  // namespace
+
+template <>
+RXCfg RLaunch<T>::x_r2c(const RAxis& a, int n1, int n2) {
+  return x_shape(a, n1, n2, [&](RXCfg& c) {
+    c.threads = r_spread<T>(a, c.xt.np, r_threads<T>(a, c.xt.np, false),
+                            (long long)c.xt.nbj * n2);
+    const size_t lines = sizeof(cpx<T>) * (size_t)c.xt.np * c.xt.ls;
+    c.lds = sizeof(cpx<T>) * (size_t)a.m + (lines < 256 ? 256 : lines);
+  });
+}
+
+template <>
+RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
+  auto with = [&](int rows, int most) {
+    return x_shape(a, n1, n2, [&](RXCfg& c) {
+      const int tl = 2 * c.xt.np;
+      const int sweep = (tl * ((a.n + rows - 1) / rows) + 63) / 64 * 64;
+      const int fft = r_spread<T>(a, c.xt.np, r_threads<T>(a, c.xt.np, false),
+                                  (long long)c.xt.nbj * n2);
+      c.xt.S = rows;
+      c.xt.P = sweep / tl;
+      c.threads = sweep > fft ? sweep : fft;
+      if (c.threads > most) c.threads = 1 << 20;  // no such shape
+      const size_t v = (size_t)a.m + (size_t)tl * c.xt.ls + 2 * (size_t)(sweep / 64) * tl +
+                       (size_t)c.xt.P * (rows + kSweepGains);
+      c.lds = sizeof(cpx<T>) * v;
+      const size_t least = sizeof(cpx<T>) * (size_t)a.m + 1024;  // the reduction
+      if (c.lds < least) c.lds = least;
+    });
+  };
+  // FP32 grids that fill the GPU sweep in chunks of 16 rows, so that a block of 512 threads
+  // takes 16 lines and two share a CU (400^3: 477 us, 696 with 8 rows); smaller ones in
+  // shorter chains of 8 (101x75x63: 20.0 us against 21.6).
+  if (F32) {
+    const RXCfg c = with(16, 512);
+    if (c.blocks >= 1024) return c;
+  }
+  return with(8, r_max_threads<T>());
+}
+
+template <>
+hipError_t RLaunch<T>::r2c(hipStream_t st, const RXCfg& c, const RAxis& a, const cpx<T>* psi,
+                           cpx<T>* spec, const RProgram* p, double* part) {
+  if (c.blocks < 1) return hipErrorInvalidValue;
+  if (a.maxr == kSmall)
+    hipLaunchKernelGGL((k_rr2c<T, kSmall>), dim3(c.blocks), dim3(c.threads), c.lds, st, psi, spec,
+                       c.xt, p, part);
+  else
+    hipLaunchKernelGGL((k_rr2c<T, kBig>), dim3(c.blocks), dim3(c.threads), c.lds, st, psi, spec,
+                       c.xt, p, part);
+  return hipGetLastError();
+}
+
+template <>
+hipError_t RLaunch<T>::c2r(hipStream_t st, const RXCfg& c, const RAxis& a, int mode,
+                           const cpx<T>* spec, const RProgram* p, const RXArgs<T>& g) {
+  if (c.blocks < 1) return hipErrorInvalidValue;
+#define GP_C2R(R, MD, SV)                                                                    \
+  hipLaunchKernelGGL((k_rc2r<T, R, MD, SV>), dim3(c.blocks), dim3(c.threads), c.lds, st, spec, \
+                     c.xt, p, g)
+#define GP_C2R_MODE(MD)                                            \
+  case MD:                                                         \
+    if (a.maxr != kSmall) GP_C2R(kBig, MD, 8);                     \
+    else if (F32 && c.xt.S == 16) GP_C2R(kSmall, MD, (F32 ? 16 : 8)); \
+    else GP_C2R(kSmall, MD, 8);                                    \
+    break;
+  switch (mode) {
+    GP_C2R_MODE(MODE_IMAG)
+    GP_C2R_MODE(MODE_REAL)
+    case MODE_OBSERVE:
+      if (a.maxr != kSmall) GP_C2R(kBig, MODE_OBSERVE, 8);
+      else GP_C2R(kSmall, MODE_OBSERVE, 8);
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef GP_C2R_MODE
+#undef GP_C2R
+  return hipGetLastError();
+}
+#endif
 
 }  // namespace gpdbec

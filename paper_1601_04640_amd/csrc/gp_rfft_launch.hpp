@@ -5,11 +5,28 @@
 #include <stddef.h>
 
 #include "gp_rfft.hpp"
+#include "gp_rx.hpp"
+#include "gp_sweep_launch.hpp"
 
 namespace gpdbec {
 
 // LDS a block may take (of 160 KiB per CU).
 constexpr size_t kRLds = 143360;
+
+// Shape of an x pass: its tile, blocks, threads and LDS bytes; blocks = 0: none.
+struct RXCfg {
+  RXTile xt{};
+  int blocks = 0, threads = 0;
+  size_t lds = 0;
+  // the sweep's shape as the gain tables see it (rows, lines per block, whole waves)
+  SweepCfg sweep() const {
+    SweepCfg c;
+    c.S = blocks ? xt.S : 0;
+    c.TC = 2 * xt.np;
+    c.threads = c.TC * xt.P;
+    return c;
+  }
+};
 
 template <typename T>
 struct RLaunch {
@@ -21,6 +38,14 @@ struct RLaunch {
   // whether an axis's lines have these passes, contiguous or strided
   static bool contiguous_ok(const RAxis& a);
   static bool strided_ok(const RAxis& a, int cols);
+  // the x passes of a grid whose x axis is a: real-to-complex, and complex-to-real with the
+  // sub-step and the sweep (gains: its table)
+  static RXCfg x_r2c(const RAxis& a, int n1, int n2);
+  static RXCfg x_c2r(const RAxis& a, int n1, int n2);
+  static hipError_t r2c(hipStream_t st, const RXCfg& c, const RAxis& a, const cpx<T>* psi,
+                        cpx<T>* spec, const RProgram* p, double* part);
+  static hipError_t c2r(hipStream_t st, const RXCfg& c, const RAxis& a, int mode,
+                        const cpx<T>* spec, const RProgram* p, const RXArgs<T>& g);
   // contiguous lines of a.n points (nlines of them); scale, ktab: the convolution's
   static hipError_t contiguous(hipStream_t st, cpx<T>* data, int nlines, const RAxis& a,
                                const RProgram* p, const T* ktab, const double* scale);
@@ -35,6 +60,12 @@ struct RLaunch {
   template <> hipError_t RLaunch<T>::program(hipStream_t, const RAxis&, int, const void*,      \
                                              const void*, const void*, RProgram*);             \
   template <> bool RLaunch<T>::contiguous_ok(const RAxis&);                                    \
+  template <> RXCfg RLaunch<T>::x_r2c(const RAxis&, int, int);                                 \
+  template <> RXCfg RLaunch<T>::x_c2r(const RAxis&, int, int);                                 \
+  template <> hipError_t RLaunch<T>::r2c(hipStream_t, const RXCfg&, const RAxis&,              \
+                                         const cpx<T>*, cpx<T>*, const RProgram*, double*);    \
+  template <> hipError_t RLaunch<T>::c2r(hipStream_t, const RXCfg&, const RAxis&, int,         \
+                                         const cpx<T>*, const RProgram*, const RXArgs<T>&);    \
   template <> bool RLaunch<T>::strided_ok(const RAxis&, int);                                  \
   template <> hipError_t RLaunch<T>::contiguous(hipStream_t, cpx<T>*, int, const RAxis&,       \
                                                 const RProgram*, const T*, const double*);     \

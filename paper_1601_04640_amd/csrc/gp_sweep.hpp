@@ -29,16 +29,17 @@ namespace gpdbec {
 // stored values, nothing written.
 enum : int { SWEEP_SOLVE = 0, SWEEP_SUMS = 1, SWEEP_OBS = 2 };
 
-// Gains per chunk in the table: the scan steps forward (1, 2, 4, 8 chunks), the carry into
-// the wave's chunk, the same backward, and the wave's total (QW <= 16 chunks per wave).
-constexpr int kSweepGains = 11;
+// Gains per chunk in the table: the scan steps forward (1, 2, 4, 8, 16 chunks), the carry
+// into the wave's chunk, the same backward, and the wave's total (QW <= 32 chunks per wave).
+constexpr int kSweepGains = 13;
+enum : int { SG_UP = 0, SG_UP_IN = 5, SG_DOWN = 6, SG_DOWN_IN = 11, SG_WAVE = 12 };
 
 // Tables of a sweep, one per factor set (block b: set b): for chunk q (S rows, QW chunks of
 // a column per wave) the products of g:
-//   [s P + q]        over the chunks q, q-1, .. of the wave that step s composes
-//   [(4) P + q]      over the chunks before q in its wave (1 for the first)
-//   [(5 + s) P + q]  over q, q+1, .. of the wave     [(9) P + q]  over those after q
-//   [(10) P + q]     over the whole wave
+//   [(SG_UP + s) P + q]    over the chunks q, q-1, .. of the wave that step s composes
+//   [SG_UP_IN P + q]       over the chunks before q in its wave (1 for the first)
+//   [(SG_DOWN + s) P + q]  over q, q+1, ..     [SG_DOWN_IN P + q]  over those after q
+//   [SG_WAVE P + q]        over the whole wave
 // from the rounded factors, in FP64.  One thread per chunk, P <= 256 threads; P counts the
 // chunks of whole waves (those past the line have the identity map).
 struct SweepTables {
@@ -71,14 +72,14 @@ __global__ void __launch_bounds__(256) k_sweep_gains(SweepTables t, int N, int S
     for (int c = a; c <= b; ++c) mul(r, i, gr[c], gi[c]);
     return cpx<T>{(T)r, (T)i};
   };
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < 5; ++s) {
     const int n = 1 << s;
-    w[s * P + q] = over(q - n + 1 > first ? q - n + 1 : first, q);
-    w[(5 + s) * P + q] = over(q, q + n - 1 < last ? q + n - 1 : last);
+    w[(SG_UP + s) * P + q] = over(q - n + 1 > first ? q - n + 1 : first, q);
+    w[(SG_DOWN + s) * P + q] = over(q, q + n - 1 < last ? q + n - 1 : last);
   }
-  w[4 * P + q] = over(first, q - 1);
-  w[9 * P + q] = over(q + 1, last);
-  w[10 * P + q] = over(first, last);
+  w[SG_UP_IN * P + q] = over(first, q - 1);
+  w[SG_DOWN_IN * P + q] = over(q + 1, last);
+  w[SG_WAVE * P + q] = over(first, last);
 }
 
 // A complex value through a buffer descriptor: `off` in bytes; out of range reads as zero
@@ -92,6 +93,14 @@ __device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t r, unsigned off,
   typedef unsigned u4 __attribute__((ext_vector_type(4)));
   const u4 t = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
   v = cpx<double>{__hiloint2double((int)t.y, (int)t.x), __hiloint2double((int)t.w, (int)t.z)};
+}
+__device__ __forceinline__ void buf_load_real(__amdgpu_buffer_rsrc_t r, unsigned off, float& v) {
+  v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void buf_load_real(__amdgpu_buffer_rsrc_t r, unsigned off, double& v) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const u2 t = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+  v = __hiloint2double((int)t.y, (int)t.x);
 }
 __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, unsigned off, cpx<float> v) {
   typedef unsigned u2 __attribute__((ext_vector_type(2)));
@@ -212,15 +221,15 @@ __global__ void __launch_bounds__(MAXT, WPE) k_sweep(cpx<T>* __restrict__ psi,
     for (int s = 0; s < NS; ++s) {
       const int off = TC << s;
       const cpx<T> Dn = lane_at(D, (lane - off) * 4);
-      D = csel(lane >= off, D + mulg(gs[s * P + q], Dn), D);
+      D = csel(lane >= off, D + mulg(gs[(SG_UP + s) * P + q], Dn), D);
     }
     if (lane >= 64 - TC) wD[wave * TC + c] = D;
     const cpx<T> Du = lane_at(D, (lane - TC) * 4);
     __syncthreads();
     cpx<T> C = zero;
     for (int w = 0; w < wave; ++w)
-      C = wD[w * TC + c] + mulg(gs[10 * P + w * QW], C);
-    cpx<T> d = csel(lane < TC, C, Du + mulg(gs[4 * P + q], C));
+      C = wD[w * TC + c] + mulg(gs[SG_WAVE * P + w * QW], C);
+    cpx<T> d = csel(lane < TC, C, Du + mulg(gs[SG_UP_IN * P + q], C));
 #pragma unroll
     for (int e = 0; e < S; ++e) {
       d = r[e] + mulg(fq[e], d);
@@ -234,15 +243,15 @@ __global__ void __launch_bounds__(MAXT, WPE) k_sweep(cpx<T>* __restrict__ psi,
     for (int s = 0; s < NS; ++s) {
       const int off = TC << s;
       const cpx<T> Xn = lane_at(X, (lane + off) * 4);
-      X = csel(lane + off < 64, X + mulg(gs[(5 + s) * P + q], Xn), X);
+      X = csel(lane + off < 64, X + mulg(gs[(SG_DOWN + s) * P + q], Xn), X);
     }
     if (lane < TC) wX[wave * TC + c] = X;
     const cpx<T> Xd = lane_at(X, (lane + TC) * 4);
     __syncthreads();
     cpx<T> E = zero;
     for (int w = nw - 1; w > wave; --w)
-      E = wX[w * TC + c] + mulg(gs[10 * P + w * QW], E);
-    cpx<T> x = csel(lane + TC >= 64, E, Xd + mulg(gs[9 * P + q], E));
+      E = wX[w * TC + c] + mulg(gs[SG_WAVE * P + w * QW], E);
+    cpx<T> x = csel(lane + TC >= 64, E, Xd + mulg(gs[SG_DOWN_IN * P + q], E));
     cpx<T> un{pr.re + (T)2 * x.re, pr.im + (T)2 * x.im};  // the next chunk's first value
 #pragma unroll
     for (int e = S - 1; e >= 0; --e) {

@@ -1,5 +1,5 @@
-"""Run-time-length line FFTs (gp_rfft.hpp): the dipolar potential of a smooth random density
-against numpy's FFTs, with y and z lengths that take every radix, every tile width and
+"""Run-time-length FFTs (gp_rfft.hpp, gp_rx.hpp): the dipolar potential of a random density
+against numpy's FFTs, with x, y and z lengths that take every radix, every tile width and
 Bluestein's algorithm.
 
 An FFT's error grows with the stages: the potential is held to 16 units in the last place
@@ -12,13 +12,16 @@ from tests.gpu_util import banner, oparams
 
 pytestmark = pytest.mark.gpu
 
-# (nx, ny, nz); the x length keeps the grid off the specialised passes
+# (nx, ny, nz); at least one length keeps the grid off the specialised passes
 GRIDS = [
     (18, 22, 26), (18, 28, 33), (18, 34, 36), (18, 37, 39), (18, 42, 45), (18, 49, 50),
     (18, 54, 63), (18, 66, 70), (18, 74, 77), (18, 81, 91), (18, 100, 121), (18, 126, 143),
     (18, 135, 169), (18, 144, 196), (18, 210, 225), (18, 97, 101),
     (18, 14, 600), (18, 9, 1100), (18, 14, 397),       # narrower strided tiles, Bluestein
     (18, 601, 14), (22, 1024, 1), (22, 2000, 1), (22, 1999, 1), (22, 1331, 1), (22, 1093, 1),
+    (26, 15, 18), (37, 18, 20), (63, 17, 18), (77, 34, 15), (100, 9, 18), (121, 18, 7), (169, 18, 9),
+    (225, 33, 8), (397, 18, 10), (600, 21, 9), (1024, 18, 1), (1331, 21, 1), (2000, 19, 1),
+    (1999, 18, 1), (144, 130, 70),
 ]
 
 

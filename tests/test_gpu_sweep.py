@@ -1,5 +1,6 @@
-"""Strided Crank-Nicolson sweeps (gp_sweep.hpp): every chunk and column shape, at the edges of
-its range, on states whose step is known line by line.
+"""Crank-Nicolson sweeps along strided axes (gp_sweep.hpp) and along x (gp_rx.hpp): every
+chunk and column shape, at the edges of its range, on states whose step is known line by
+line.
 
 Without couplings and trap a step of a product state X(x) Y(y) Z(z) is the product of the
 three one-dimensional Crank-Nicolson steps, which scipy's banded solver gives in FP64.  A
@@ -25,6 +26,16 @@ SHAPES = [
     ("2dxz", (50, 1, 1022), "fp64"),   # quarter-width tiles
     ("2dxy", (50, 1026, 1), "fp64"),   # 16-row chunks, quarter-width tiles
     ("2dxy", (21, 2048, 1), "fp64"),   # the longest lines
+    # along x: one line over a tile, several waves, 16-row chunks, the longest lines
+    ("3d", (18, 17, 66), "fp32"),
+    ("3d", (130, 19, 34), "fp32"),
+    ("3d", (66, 70, 500), "fp32"),
+    ("2dxy", (1030, 22, 1), "fp32"),
+    ("2dxy", (2046, 21, 1), "fp32"),
+    ("3d", (130, 19, 34), "fp64"),
+    ("3d", (66, 33, 70), "fp64"),
+    ("2dxz", (1022, 1, 23), "fp64"),
+    ("2dxy", (2046, 21, 1), "fp64"),
     ("3d", (301, 290, 200), "fp64"),   # an array past 256 MiB with a ragged pitch
 ]
 

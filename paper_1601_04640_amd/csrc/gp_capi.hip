@@ -146,7 +146,8 @@ int tjw_of(bool fp64, int n) { return fp64 ? Launch<double>::tjw(n) : Launch<flo
 int tc_of(bool fp64, int n) { return fp64 ? Launch<double>::tc(n) : Launch<float>::tc(n); }
 int tv_of(bool fp64, int n) { return fp64 ? Launch<double>::tv(n) : Launch<float>::tv(n); }
 
-Layout make_layout(const gp_params* p, unsigned host = 0) {
+// batch: an instance of an ensemble (its sweeps are the batched passes')
+Layout make_layout(const gp_params* p, unsigned host = 0, bool batch = false) {
   Layout L{};
   const bool fp64 = p->prec == GP_FP64;
   L.n0 = p->nx;
@@ -163,13 +164,22 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
   const int H = L.n0 / 2 + 1;
   L.nspec = (size_t)H * L.n1 * L.n2;
   L.generic = is_generic(p);
-  if (L.generic) {
+  {
     const long long row = L.n0, plane = (long long)L.n0 * L.n1;
     L.sw[1] = fp64 ? SweepLaunch<double>::cfg(L.n1, L.n0, L.n2, row)
                    : SweepLaunch<float>::cfg(L.n1, L.n0, L.n2, row);
     if (p->geom == GP_3D)
       L.sw[2] = fp64 ? SweepLaunch<double>::cfg(L.n2, L.n0, L.n1, plane)
                      : SweepLaunch<float>::cfg(L.n2, L.n0, L.n1, plane);
+    // Specialised lengths have the LDS-staged sweeps as well, whose scans move through DPP.
+    // The register sweeps are ahead from 256 points in FP32 (256^2: 5.1 us against 6.5, 256^3
+    // 45-48 against 46-51, 480^3 380 against 817) and from 128 points in FP64 where the grid
+    // fills the GPU (128^3 11.0-12.6 against 12.7-15.2, 256^3 91-93 against 94); shorter or
+    // fewer lines wait on the scan (FP64 64^3 5.7 against 4.3, 512x384 7.2 against 6.6).
+    for (int a = 1; a < 3 && !L.generic; ++a) {
+      const int n = a == 1 ? L.n1 : L.n2;
+      if (batch || n < (fp64 ? 128 : 256) || (fp64 && L.sw[a].blocks < 512)) L.sw[a] = SweepCfg{};
+    }
   }
   const int ns0[2] = {L.n0, L.n1};
   bool lng[2] = {false, false};
@@ -255,7 +265,10 @@ Layout make_layout(const gp_params* p, unsigned host = 0) {
     L.nb_x = ((L.n1 + tj - 1) / tj) * L.n2;
     L.nb_nl = L.nb_x;   // the x pass writes both
     L.nb_r2c = ((L.n1 + tjw - 1) / tjw) * L.n2;
-    if (p->geom == GP_3D) {
+    const int last = p->geom == GP_3D ? 2 : 1;
+    if (L.sw[last].S) {
+      L.nb_col = L.sw[last].blocks;
+    } else if (p->geom == GP_3D) {
       const int tcz = tc_of(fp64, L.n2);
       L.nb_col = ((L.n0 + tcz - 1) / tcz) * L.n1;   // z sweep / z observe
     } else {
@@ -758,19 +771,26 @@ struct Passes {
       const int nl = H * L.n2;
       const int lb = c->fp64 ? Launch<double>::lbf(L.n1) : Launch<float>::lbf(L.n1);
       const int tc = tv_of(c->fp64, L.n2);
+      // the lines per XCD as the convolution takes them: the inverse ones while the spectrum
+      // fits the L2s at all, the forward ones also not in spectra so small that either order
+      // finds them there (128x96x80 FP32: 4.9 us in dispatch order, 6.0 so; the convolution
+      // gains 0.3)
+      const size_t sb = 2 * L.esz * L.nspec;
+      const int inv_xcd = sb <= ((size_t)64 << 20), fwd_xcd = inv_xcd && sb >= ((size_t)8 << 20);
       if (fin2) {
         GP_HIP(Launch<T>::fft_line_fin(L.n1, (nl + lb - 1) / lb, c->st, spec(c), tw(c, 1), nl,
-                                       *fin2, fin_mode));
+                                       fwd_xcd, *fin2, fin_mode));
       } else {
         GP_PASS(c, GP_PASS_FFT_Y_FWD,
                 Launch<T>::fft_line(L.n1, false, (nl + lb - 1) / lb, c->st, spec(c), tw(c, 1),
-                                    nl));
+                                    nl, fwd_xcd));
       }
       GP_PASS(c, GP_PASS_CONV_Z,
               Launch<T>::conv_col(L.n2, ((L.n1 + tc - 1) / tc) * H, c->st, spec(c),
                                   Kp(c), scale, tw(c, 2), L.n1));
       GP_PASS(c, GP_PASS_FFT_Y_INV,
-              Launch<T>::fft_line(L.n1, true, (nl + lb - 1) / lb, c->st, spec(c), tw(c, 1), nl));
+              Launch<T>::fft_line(L.n1, true, (nl + lb - 1) / lb, c->st, spec(c), tw(c, 1), nl,
+                                  inv_xcd));
     } else {
       const int lb = c->fp64 ? Launch<double>::lb(L.n1) : Launch<float>::lb(L.n1);
       GP_PASS(c, GP_PASS_CONV_Y,
@@ -810,14 +830,8 @@ struct Passes {
                "the adjoint step needs axis lengths with specialised passes");
       return GP_E_SIZE;
     }
-    const int tcy = tc_of(c->fp64, L.n1);
-    const int nb_y = ((L.n0 + tcy - 1) / tcy) * L.n2;
-    if (c->p.geom == GP_3D) {
-      GP_HIP(Launch<T>::cn_col(L.n2, MODE_ADJ, false, L.nb_col, c->st, lam, cn(c, 2, 2), nullptr, L.n0, (size_t)L.n0 * L.n1,
-                               (size_t)L.n0));
-    }
-    GP_HIP(Launch<T>::cn_col(L.n1, MODE_ADJ, false, nb_y, c->st, lam, cn(c, 1, 2), nullptr, L.n0, (size_t)L.n0,
-                             (size_t)L.n0 * L.n1));
+    if (c->p.geom == GP_3D) GP_TRY(col_sweep(c, 2, MODE_ADJ, false, lam));
+    GP_TRY(col_sweep(c, 1, MODE_ADJ, false, lam));
     GP_TRY(convolution(c, psin, &c->sc()->one));
     const StepScalars sx = step_scalars(c);
     T* sf = c->at<T>(L.o_sfield);
@@ -854,10 +868,28 @@ struct Passes {
       GP_TRY(g_sweep(c, 2, 0, 2));
       return finalize(c, fin_mode);
     }
-    GP_HIP(Launch<T>::cn_col(L.n2, MODE_OBSERVE, true, L.nb_col, c->st, psi(c), nullptr,
-                             c->at<double>(L.o_pcol), L.n0, (size_t)L.n0 * L.n1,
-                             (size_t)L.n0));
+    GP_TRY(col_sweep(c, 2, MODE_OBSERVE, true, psi(c)));
     return finalize(c, fin_mode);
+  }
+
+  // Sweep of axis 1 or 2 of `data` on a grid of specialised lengths (mode MODE_*; sums of the
+  // new state into o_pcol, or with MODE_OBSERVE of the stored one)
+  static gp_status col_sweep(gp_ctx* c, int axis, int mode, bool sums, cpx<T>* data) {
+    const Layout& L = c->L;
+    const int k = mode == MODE_IMAG ? 0 : mode == MODE_ADJ ? 2 : 1, n = axis == 1 ? L.n1 : L.n2;
+    const size_t plane = (size_t)L.n0 * L.n1, es = axis == 1 ? L.n0 : plane,
+                 os = axis == 1 ? plane : L.n0;
+    double* pc = sums ? c->at<double>(L.o_pcol) : nullptr;
+    const cpx<T>* f = mode == MODE_OBSERVE ? nullptr : cn(c, axis, k);
+    if (L.sw[axis].S)
+      return dev(SweepLaunch<T>::run(
+          L.sw[axis], mode == MODE_OBSERVE ? SWEEP_OBS : sums ? SWEEP_SUMS : SWEEP_SOLVE, k != 0,
+          c->st, data, f, c->at<cpx<T>>(L.o_sw[axis][k]), pc, n, L.n0, (long long)es,
+          (long long)os));
+    const int tc = tc_of(c->fp64, n);
+    return dev(Launch<T>::cn_col(n, mode, sums, (L.n0 + tc - 1) / tc * (axis == 1 ? L.n2 : L.n1),
+                                 c->st, data, f, pc, L.n0, es, os,
+                                 axis == 1 && c->p.geom == GP_3D));
   }
 
   static gp_status step(gp_ctx* c, bool imag) {
@@ -909,21 +941,14 @@ struct Passes {
                          c->sc()->span);
       GP_HIP(hipGetLastError());
     }
-    const int tcy = tc_of(c->fp64, L.n1);
-    if (c->p.geom == GP_3D) {
-      GP_PASS(c, GP_PASS_CN_Y,
-              Launch<T>::cn_col(L.n1, mode, false, ((L.n0 + tcy - 1) / tcy) * L.n2, c->st,
-                                psi(c), cn(c, 1, k), nullptr, L.n0, (size_t)L.n0,
-                                (size_t)L.n0 * L.n1));
-      GP_PASS(c, GP_PASS_CN_Z,
-              Launch<T>::cn_col(L.n2, mode, true, L.nb_col, c->st, psi(c), cn(c, 2, k),
-                                c->at<double>(L.o_pcol), L.n0, (size_t)L.n0 * L.n1,
-                                (size_t)L.n0));
-    } else {
-      GP_PASS(c, GP_PASS_CN_Y,
-              Launch<T>::cn_col(L.n1, mode, true, L.nb_col, c->st, psi(c), cn(c, 1, k),
-                                c->at<double>(L.o_pcol), L.n0, (size_t)L.n0,
-                                (size_t)L.n0 * L.n1));
+    const bool is3d = c->p.geom == GP_3D;
+    GP_TRY(pass_begin(c, GP_PASS_CN_Y));
+    GP_TRY(col_sweep(c, 1, mode, !is3d, psi(c)));
+    GP_TRY(pass_end(c, GP_PASS_CN_Y));
+    if (is3d) {
+      GP_TRY(pass_begin(c, GP_PASS_CN_Z));
+      GP_TRY(col_sweep(c, 2, mode, true, psi(c)));
+      GP_TRY(pass_end(c, GP_PASS_CN_Z));
     }
     if (defer) {
       c->fin_pending = true;
@@ -938,7 +963,6 @@ struct Passes {
   static gp_status launch_pass(gp_ctx* c, int pass) {
     const Layout& L = c->L;
     if (L.generic) return GP_E_ARG;
-    const int tcy = tc_of(c->fp64, L.n1);
     switch (pass) {
       case GP_PASS_R2C_X:
         return dev(Launch<T>::r2c_x(L.n0, L.nb_r2c, c->st, psi(c), spec(c),
@@ -949,18 +973,10 @@ struct Passes {
                                          cn(c, 0, 1), step_scalars(c), c->at<double>(L.o_pnl),
                                          nullptr, L.n1, L.n2));
       case GP_PASS_CN_Y:
-        if (c->p.geom == GP_3D)
-          return dev(Launch<T>::cn_col(L.n1, MODE_REAL, false, ((L.n0 + tcy - 1) / tcy) * L.n2,
-                                       c->st, psi(c), cn(c, 1, 1), nullptr,
-                                       L.n0, (size_t)L.n0, (size_t)L.n0 * L.n1));
-        return dev(Launch<T>::cn_col(L.n1, MODE_REAL, true, L.nb_col, c->st, psi(c), cn(c, 1, 1),
-                                     c->at<double>(L.o_pcol), L.n0,
-                                     (size_t)L.n0, (size_t)L.n0 * L.n1));
+        return col_sweep(c, 1, MODE_REAL, c->p.geom != GP_3D, psi(c));
       case GP_PASS_CN_Z:
         if (c->p.geom != GP_3D) return GP_E_ARG;
-        return dev(Launch<T>::cn_col(L.n2, MODE_REAL, true, L.nb_col, c->st, psi(c), cn(c, 2, 1),
-                                     c->at<double>(L.o_pcol), L.n0,
-                                     (size_t)L.n0 * L.n1, (size_t)L.n0));
+        return col_sweep(c, 2, MODE_REAL, true, psi(c));
       default:
         return GP_E_ARG;
     }
@@ -1493,7 +1509,7 @@ BatchLayout batch_layout(const gp_params* arr, int count) {
   o += align_up(sizeof(WorkItem) * (size_t)B.total_items);
   for (int i = 0; i < count; ++i) {
     B.o_inst.push_back(o);
-    o += align_up(make_layout(&arr[i]).total);
+    o += align_up(make_layout(&arr[i], 0, true).total);
   }
   B.total = o;
   return B;
@@ -1694,6 +1710,38 @@ gp_status batch_run(gp_batch* b, int nsteps, bool imag) {
   return GP_OK;
 }
 
+// A context over a workspace of layout L (maps: device addresses of host-resident V and
+// kernel table, or null).
+gp_status init_ctx(const gp_params* params, unsigned host, const Layout& L, void* dev_workspace,
+                   void* const (&maps)[2], void* hip_stream, gp_ctx** out) {
+  gp_ctx* c = new (std::nothrow) gp_ctx();
+  if (!c) return GP_E_NOMEM;
+  c->p = *params;
+  c->L = L;
+  c->st = reinterpret_cast<hipStream_t>(hip_stream);
+  c->ws = reinterpret_cast<char*>(dev_workspace);
+  c->fp64 = params->prec == GP_FP64;
+  c->psi_set = false;
+  c->ekz_valid = false;
+  c->gc = contact(c->p);
+  c->hostV = reinterpret_cast<char*>(maps[0]);
+  c->hostK = reinterpret_cast<char*>(maps[1]);
+  int devid = 0;
+  if (hipGetDevice(&devid) != hipSuccess ||
+      hipDeviceGetAttribute(&c->clock_khz, hipDeviceAttributeWallClockRate, devid) != hipSuccess)
+    c->clock_khz = 0;
+  clear_stale_error();
+  gp_status s = c->fp64 ? Passes<double>::init_tables(c) : Passes<float>::init_tables(c);
+  // the tables written through a host mapping are complete before the call returns
+  if (s == GP_OK && host) s = dev(hipStreamSynchronize(c->st));
+  if (s != GP_OK) {
+    delete c;
+    return s;
+  }
+  *out = c;
+  return GP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1747,32 +1795,7 @@ gp_status gp_init_ex(const gp_params* params, unsigned host, void* dev_workspace
     }
     GP_HIP(hipHostGetDevicePointer(&maps[k], hp[k], 0));
   }
-  gp_ctx* c = new (std::nothrow) gp_ctx();
-  if (!c) return GP_E_NOMEM;
-  c->p = *params;
-  c->L = L;
-  c->st = reinterpret_cast<hipStream_t>(hip_stream);
-  c->ws = reinterpret_cast<char*>(dev_workspace);
-  c->fp64 = params->prec == GP_FP64;
-  c->psi_set = false;
-  c->ekz_valid = false;
-  c->gc = contact(c->p);
-  c->hostV = reinterpret_cast<char*>(maps[0]);
-  c->hostK = reinterpret_cast<char*>(maps[1]);
-  int devid = 0;
-  if (hipGetDevice(&devid) != hipSuccess ||
-      hipDeviceGetAttribute(&c->clock_khz, hipDeviceAttributeWallClockRate, devid) != hipSuccess)
-    c->clock_khz = 0;
-  clear_stale_error();
-  gp_status s = c->fp64 ? Passes<double>::init_tables(c) : Passes<float>::init_tables(c);
-  // the tables written through a host mapping are complete before the call returns
-  if (s == GP_OK && host) s = dev(hipStreamSynchronize(c->st));
-  if (s != GP_OK) {
-    delete c;
-    return s;
-  }
-  *out = c;
-  return GP_OK;
+  return init_ctx(params, host, L, dev_workspace, maps, hip_stream, out);
 }
 
 gp_status gp_init(const gp_params* params, void* dev_workspace, size_t ws_bytes, void* hip_stream,
@@ -2074,7 +2097,9 @@ gp_status gp_batch_init(const gp_params* params, int count, void* dev_workspace,
   gp_status s = GP_OK;
   for (int i = 0; i < count && s == GP_OK; ++i) {
     gp_ctx* c = nullptr;
-    s = gp_init(&params[i], b->ws + BL.o_inst[i], make_layout(&params[i]).total, hip_stream, &c);
+    void* const maps[2] = {nullptr, nullptr};
+    s = init_ctx(&params[i], 0u, make_layout(&params[i], 0, true), b->ws + BL.o_inst[i], maps,
+                 hip_stream, &c);
     if (s == GP_OK) b->inst.push_back(c);
   }
   b->work_base = reinterpret_cast<WorkItem*>(b->ws + BL.o_work);

@@ -158,15 +158,15 @@ hipError_t Launch<T>::adj_fin(int n0, int blocks, hipStream_t st, cpx<T>* lam,
 #if GP_FAMILY == 1
 template <>
 hipError_t Launch<T>::fft_line_fin(int n, int blocks, hipStream_t st, cpx<T>* data,
-                                   const cpx<T>* tw, int nlines, const FinArgs& fa,
-                                   int fin_mode) {
+                                   const cpx<T>* tw, int nlines, int xcd,
+                                   const FinArgs& fa, int fin_mode) {
   switch (n) {
 #define X(N)                                                                               \
   case N:                                                                                  \
     if (fin_mode == FIN_IMAG)                                                              \
-      GP_LAUNCH((k_fft_line_fin<T, N, FIN_IMAG>), blocks + kFinLead, st, data, tw, nlines, fa); \
+      GP_LAUNCH((k_fft_line_fin<T, N, FIN_IMAG>), blocks + kFinLead, st, data, tw, nlines, xcd, fa); \
     else                                                                                   \
-      GP_LAUNCH((k_fft_line_fin<T, N, FIN_REAL>), blocks + kFinLead, st, data, tw, nlines, fa); \
+      GP_LAUNCH((k_fft_line_fin<T, N, FIN_REAL>), blocks + kFinLead, st, data, tw, nlines, xcd, fa); \
     break;
     GP_FOR_SIZES(X)
 #undef X
@@ -178,14 +178,14 @@ hipError_t Launch<T>::fft_line_fin(int n, int blocks, hipStream_t st, cpx<T>* da
 
 template <>
 hipError_t Launch<T>::fft_line(int n, bool inv, int blocks, hipStream_t st, cpx<T>* data,
-                               const cpx<T>* tw, int nlines) {
+                               const cpx<T>* tw, int nlines, int xcd) {
   switch (n) {
 #define X(N)                                                                    \
   case N:                                                                       \
     if (inv)                                                                    \
-      GP_LAUNCH((k_fft_line<T, N, true>), blocks, st, data, tw, nlines);        \
+      GP_LAUNCH((k_fft_line<T, N, true>), blocks, st, data, tw, nlines, xcd);        \
     else                                                                        \
-      GP_LAUNCH((k_fft_line<T, N, false>), blocks, st, data, tw, nlines);       \
+      GP_LAUNCH((k_fft_line<T, N, false>), blocks, st, data, tw, nlines, xcd);       \
     break;
     GP_FOR_SIZES(X)
 #undef X
@@ -232,9 +232,9 @@ hipError_t Launch<T>::conv_col(int n2, int blocks, hipStream_t st, cpx<T>* spec,
 template <>
 hipError_t Launch<T>::cn_col(int n, int mode, bool sums, int blocks, hipStream_t st,
                              cpx<T>* psi, const cpx<T>* cnm, double* part, int n0,
-                             size_t estride, size_t ostride) {
+                             size_t estride, size_t ostride, int xcd) {
 #define CN(N, M, S) \
-  GP_LAUNCH((k_cn_col<T, N, M, S>), blocks, st, psi, cnm, part, n0, estride, ostride)
+  GP_LAUNCH((k_cn_col<T, N, M, S>), blocks, st, psi, cnm, part, n0, estride, ostride, xcd)
   switch (n) {
 #define X(N)                                        \
   case N:                                           \

@@ -31,14 +31,15 @@ struct Launch {
   static hipError_t r2c_x(int n0, int blocks, hipStream_t st, const cpx<T>* psi, cpx<T>* spec,
                           const cpx<T>* tw0, double* part, int n1, int n2);
   static hipError_t fft_line(int n, bool inv, int blocks, hipStream_t st, cpx<T>* data,
-                             const cpx<T>* tw, int nlines);
+                             const cpx<T>* tw, int nlines, int xcd);
   // a step's x R2C / forward y FFT carrying the previous step's finalisation (mode
   // fin_mode; nfin blocks: 1 finalize block, or the first-stage slices)
   static hipError_t r2c_x_fin(int n0, int blocks, hipStream_t st, const cpx<T>* psi,
                               cpx<T>* spec, const cpx<T>* tw0, double* part, int n1, int n2,
                               const FinArgs& fa, int fin_mode, int nfin);
   static hipError_t fft_line_fin(int n, int blocks, hipStream_t st, cpx<T>* data,
-                                 const cpx<T>* tw, int nlines, const FinArgs& fa, int fin_mode);
+                                 const cpx<T>* tw, int nlines, int xcd, const FinArgs& fa,
+                                 int fin_mode);
   static hipError_t conv_line(int n, int blocks, hipStream_t st, cpx<T>* data, const T* ktab,
                               const double* scale, const cpx<T>* tw, int nlines);
   static hipError_t conv_col(int n2, int blocks, hipStream_t st, cpx<T>* spec, const T* ktab,
@@ -61,7 +62,7 @@ struct Launch {
                             const cpx<T>* tw0, const StepScalars& sc, int n1, int n2);
   static hipError_t cn_col(int n, int mode, bool sums, int blocks, hipStream_t st, cpx<T>* psi,
                            const cpx<T>* cnm, double* part, int n0, size_t estride,
-                           size_t ostride);
+                           size_t ostride, int xcd);
 };
 
 // The members are defined (explicitly specialised) per precision in gp_inst.hip.
@@ -75,12 +76,13 @@ struct Launch {
   template <> hipError_t Launch<T>::r2c_x(int, int, hipStream_t, const cpx<T>*, cpx<T>*,      \
                                           const cpx<T>*, double*, int, int);                   \
   template <> hipError_t Launch<T>::fft_line(int, bool, int, hipStream_t, cpx<T>*,             \
-                                             const cpx<T>*, int);                              \
+                                             const cpx<T>*, int, int);                         \
   template <> hipError_t Launch<T>::r2c_x_fin(int, int, hipStream_t, const cpx<T>*, cpx<T>*,  \
                                               const cpx<T>*, double*, int, int, const FinArgs&, \
                                               int, int);                                      \
   template <> hipError_t Launch<T>::fft_line_fin(int, int, hipStream_t, cpx<T>*,              \
-                                                 const cpx<T>*, int, const FinArgs&, int);     \
+                                                 const cpx<T>*, int, int, const FinArgs&,      \
+                                                 int);                                         \
   template <> hipError_t Launch<T>::conv_line(int, int, hipStream_t, cpx<T>*, const T*,       \
                                               const double*, const cpx<T>*, int);              \
   template <> hipError_t Launch<T>::conv_col(int, int, hipStream_t, cpx<T>*, const T*,        \
@@ -100,7 +102,8 @@ struct Launch {
                                             const T*, const cpx<T>*, const cpx<T>*,             \
                                             const StepScalars&, int, int);                      \
   template <> hipError_t Launch<T>::cn_col(int, int, bool, int, hipStream_t, cpx<T>*,         \
-                                           const cpx<T>*, double*, int, size_t, size_t);
+                                           const cpx<T>*, double*, int, size_t, size_t,  \
+                                           int);
 GP_DECLARE_LAUNCH(float)
 GP_DECLARE_LAUNCH(double)
 #undef GP_DECLARE_LAUNCH

@@ -1,9 +1,9 @@
 // Batched ensemble of independent quasi-2D instances (XY or XZ planes) of uneven sizes:
-// one persistent launch per pass covers every instance.  Each launch walks a work list
-// of (instance, tile) items sorted by decreasing cost; block b takes items b, b + G,
-// b + 2G, ... (G = launched blocks, chosen by the autotuner).  The per-instance
-// descriptor points into that instance's own workspace region, laid out exactly like a
-// single-grid context, so the tile bodies are the single-grid ones.
+// one launch per pass covers every instance.  Each launch takes a work list of (instance,
+// tile) items sorted by decreasing cost: one block per item, or fewer persistent blocks
+// that walk it.  The per-instance descriptor points into that instance's own workspace
+// region, laid out like a single-grid context, so the tile bodies are the single-grid
+// ones.
 #pragma once
 #include "gp_kernels.hpp"
 
@@ -43,36 +43,74 @@ struct WorkItem {
 
 enum : int { BP_R2C = 0, BP_CONV = 1, BP_C2R = 2, BP_CN = 3, BP_COUNT = 4 };
 
-// Size classes: a single switch over all nine sizes exceeds the register allocator's
-// budget when the 384/512 bodies sit beside the smaller ones, so each pass has one
-// persistent kernel per class (<= 256 and 384/512), each over its own work list.
+// Size classes (<= 256 and 384/512), each with its own work list and kernels: persistent
+// blocks over all nine sizes spill, and tile shapes are chosen per class.
 #define GP_BATCH_CLASS0(X) X(32) X(48) X(64) X(96) X(128) X(192) X(256)
 #define GP_BATCH_CLASS1(X) X(384) X(512)
 constexpr int kBatchClasses = 2;
+constexpr int kBatchBoth = 2;  // both classes' lists in one launch (shape 0)
 __host__ __device__ constexpr int batch_class(int n) { return n > 256 ? 1 : 0; }
 
 // Dynamic LDS: the largest body of the pass and class present is requested at launch.
-// Every block walks items blockIdx.x + k gridDim.x of the work list.
-#define GP_BATCH_KERNEL(NAME, AXIS, BODY)                                              \
+//
+// What bounds these kernels is how many waves a SIMD holds while each tile's load, LDS
+// transform and store wait on each other, so registers decide.  One block per work item
+// (GP_ITEM_LOOP_KERNELS not defined; the default) leaves nothing alive across items and
+// balances the load by dispatch: against persistent blocks that walk the list, the
+// class-1 c2r takes 147 instead of 200 VGPRs and the class-1 CN 140 instead of 201 (three
+// waves per SIMD instead of two), the class-0 CN 101 instead of 134, and 192 FP32
+// instances of 96^2 to 512^2 points (13.7 M) step in 0.262 ms instead of 0.317.  The
+// persistent form (gp_batch_set_blocks below the item count) walks items
+// blockIdx.x + k gridDim.x of the list.
+//
+// Class kBatchBoth covers both classes' lists in one launch, the longer lines first:
+// their bodies need the same registers anyway (c2r 134 and 147, r2c 128 and 134 VGPRs)
+// and each pass has one drained tail instead of two (with the pairing of batch_pair_xcds,
+// 0.262 -> 0.226 ms; 16 instances 0.087 -> 0.053 ms).
+#define GP_CLASS_BODY(AXIS, BODY)                                                      \
+  if constexpr (CLS == 0) {                                                            \
+    switch (d.AXIS) { GP_BATCH_CLASS0(BODY) default: break; }                          \
+  } else if constexpr (CLS == 1) {                                                     \
+    switch (d.AXIS) { GP_BATCH_CLASS1(BODY) default: break; }                          \
+  } else {                                                                             \
+    switch (d.AXIS) { GP_BATCH_CLASS1(BODY) GP_BATCH_CLASS0(BODY) default: break; }    \
+  }
+#ifdef GP_ITEM_LOOP_KERNELS
+#define GP_BATCH_KERNEL(NAME, AXIS, BODY, WPE)                                         \
   template <typename T, int MODE, int CLS, int S>                                      \
-  __global__ __launch_bounds__(kThreads) void NAME(char* __restrict__ base,             \
-                                                   const BDesc<T>* __restrict__ D,     \
-                                                   const WorkItem* __restrict__ work,  \
-                                                   int nwork) {                        \
+  __global__ __launch_bounds__(kThreads) void NAME##_loop(                             \
+      char* __restrict__ base, const BDesc<T>* __restrict__ D,                         \
+      const WorkItem* __restrict__ work, int nwork) {                                  \
     extern __shared__ __attribute__((aligned(16))) char lds[];                         \
     constexpr int K = (MODE == MODE_REAL) ? 1 : 0;                                     \
     (void)K;                                                                           \
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {                              \
       const WorkItem item = work[w];                                                   \
       const BDesc<T>& d = D[item.inst];                                                \
-      if constexpr (CLS == 0) {                                                        \
-        switch (d.AXIS) { GP_BATCH_CLASS0(BODY) default: break; }                      \
-      } else {                                                                         \
-        switch (d.AXIS) { GP_BATCH_CLASS1(BODY) default: break; }                      \
-      }                                                                                \
+      GP_CLASS_BODY(AXIS, BODY)                                                        \
       __syncthreads();                                                                 \
     }                                                                                  \
   }
+#else
+// Block b takes work1[b], or work0[b - n1] from n1 on.  The FP32 r2c of both classes is held
+// to four waves per SIMD (128 instead of 134 VGPRs, no spill: 46.8 -> 40.8 us); c2r and CN
+// spill there and lose (80 -> 95, 53 -> 56 us).
+template <typename T, int CLS>
+constexpr int r2c_waves() { return CLS == kBatchBoth && sizeof(T) == 4 ? 4 : 1; }
+#define GP_BATCH_KERNEL(NAME, AXIS, BODY, WPE)                                         \
+  template <typename T, int MODE, int CLS, int S>                                      \
+  __global__ __launch_bounds__(kThreads, WPE) void NAME(                               \
+      char* __restrict__ base, const BDesc<T>* __restrict__ D,                         \
+      const WorkItem* __restrict__ work1, int n1, const WorkItem* __restrict__ work0) { \
+    extern __shared__ __attribute__((aligned(16))) char lds[];                         \
+    constexpr int K = (MODE == MODE_REAL) ? 1 : 0;                                     \
+    (void)K;                                                                           \
+    const int b = blockIdx.x;                                                          \
+    const WorkItem item = b < n1 ? work1[b] : work0[b - n1];                           \
+    const BDesc<T>& d = D[item.inst];                                                  \
+    GP_CLASS_BODY(AXIS, BODY)                                                          \
+  }
+#endif
 
 #define GP_BODY_R2C(N)                                                                  \
   case N:                                                                               \
@@ -100,21 +138,24 @@ __host__ __device__ constexpr int batch_class(int n) { return n > 256 ? 1 : 0; }
                                   bptr<double>(base, d.p_col), d.n0, (size_t)d.n0,        \
                                   (size_t)d.n0 * d.n1, item.tile, lds);                   \
     break;
-GP_BATCH_KERNEL(kb_r2c_x, n0, GP_BODY_R2C)
-GP_BATCH_KERNEL(kb_conv_y, n1, GP_BODY_CONV)
-GP_BATCH_KERNEL(kb_c2r_nl_cnx, n0, GP_BODY_C2R)
-GP_BATCH_KERNEL(kb_cn_y, n1, GP_BODY_CN)
+GP_BATCH_KERNEL(kb_r2c_x, n0, GP_BODY_R2C, (r2c_waves<T, CLS>()))
+GP_BATCH_KERNEL(kb_conv_y, n1, GP_BODY_CONV, 1)
+GP_BATCH_KERNEL(kb_c2r_nl_cnx, n0, GP_BODY_C2R, 1)
+GP_BATCH_KERNEL(kb_cn_y, n1, GP_BODY_CN, 1)
 #undef GP_BODY_R2C
 #undef GP_BODY_CONV
 #undef GP_BODY_C2R
 #undef GP_BODY_CN
 #undef GP_BATCH_KERNEL
+#undef GP_CLASS_BODY
 
+#ifndef GP_ITEM_LOOP_KERNELS
 // One block per instance.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void kb_finalize(const BDesc<T>* __restrict__ D,
                                                         int mode) {
   finalize_block(D[blockIdx.x].fa, mode);
 }
+#endif
 
 }  // namespace gpdbec

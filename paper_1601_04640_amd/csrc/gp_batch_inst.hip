@@ -1,6 +1,5 @@
-// Persistent multi-instance kernels for one precision (GP_REAL) and their launcher.
-// (Item-loop kernels: see thread_idx.)
-#define GP_ITEM_LOOP_KERNELS
+// Multi-instance kernels for one precision (GP_REAL), a block per work item, and the
+// launchers of these and of the persistent ones.
 #include "gp_batch.hpp"
 #include "gp_batch_launch.hpp"
 
@@ -86,13 +85,6 @@ int batch_tiles<T>(int pass, int n0, int n1, int shape) {
   return shape == 1 ? tiles_of_shape<1>(pass, n0, n1) : tiles_of_shape<0>(pass, n0, n1);
 }
 
-template <typename K>
-static hipError_t launch_dyn(K kern, int grid, size_t lds, hipStream_t st, char* base,
-                             const BDesc<T>* D, const WorkItem* work, int nwork) {
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, base, D, work, nwork);
-  return hipGetLastError();
-}
-
 // The kernel behind (pass, mode, class, shape), as an untyped function pointer.
 template <int CLS, int S>
 static const void* kernel_of(int pass, int mode) {
@@ -110,46 +102,37 @@ static const void* kernel_of(int pass, int mode) {
   }
 }
 
+static const void* item_kernel(int pass, int mode, int cls, int shape) {
+  if (cls == kBatchBoth) return kernel_of<kBatchBoth, 0>(pass, mode);
+  if (cls == 0) return shape == 0 ? kernel_of<0, 0>(pass, mode) : kernel_of<0, 1>(pass, mode);
+  return shape == 0 ? kernel_of<1, 0>(pass, mode) : kernel_of<1, 1>(pass, mode);
+}
+
 template <>
 hipError_t batch_reserve_lds<T>(int pass, int mode, int cls, int shape, size_t lds) {
-  // Raise (never lower) the kernel's dynamic-LDS limit; called outside stream capture.
+  // Raise (never lower) the kernels' dynamic-LDS limit; called outside stream capture.
   static std::mutex mu;
-  static size_t have[BP_COUNT][3][kBatchClasses][kBatchShapes] = {};
+  static size_t have[BP_COUNT][3][kBatchClasses + 1][kBatchShapes] = {};
   if (pass < 0 || pass >= BP_COUNT || mode < 0 || mode > MODE_OBSERVE || cls < 0 ||
-      cls >= kBatchClasses || shape < 0 || shape >= kBatchShapes)
+      cls > kBatchBoth || shape < 0 || shape >= kBatchShapes || (cls == kBatchBoth && shape))
     return hipErrorInvalidValue;
   std::lock_guard<std::mutex> lock(mu);
   size_t& h = have[pass][mode][cls][shape];
   if (lds <= h) return hipSuccess;
-  const void* k = cls == 0 ? (shape == 0 ? kernel_of<0, 0>(pass, mode) : kernel_of<0, 1>(pass, mode))
-                           : (shape == 0 ? kernel_of<1, 0>(pass, mode) : kernel_of<1, 1>(pass, mode));
-  const hipError_t e =
-      hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = hipFuncSetAttribute(item_kernel(pass, mode, cls, shape),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e == hipSuccess && cls != kBatchBoth)
+    e = hipFuncSetAttribute(batch_loop_kernel<T>(pass, mode, cls, shape),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e == hipSuccess) h = lds;
   return e;
 }
 
-template <int CLS, int S>
-static hipError_t launch_class(int pass, int mode, int grid, size_t lds, hipStream_t st,
-                               char* base, const BDesc<T>* D, const WorkItem* work, int nwork) {
-  switch (pass) {
-    case BP_R2C:
-      return launch_dyn(kb_r2c_x<T, 0, CLS, S>, grid, lds, st, base, D, work, nwork);
-    case BP_CONV:
-      return launch_dyn(kb_conv_y<T, 0, CLS, S>, grid, lds, st, base, D, work, nwork);
-    case BP_C2R:
-      if (mode == MODE_IMAG)
-        return launch_dyn(kb_c2r_nl_cnx<T, MODE_IMAG, CLS, S>, grid, lds, st, base, D, work, nwork);
-      if (mode == MODE_REAL)
-        return launch_dyn(kb_c2r_nl_cnx<T, MODE_REAL, CLS, S>, grid, lds, st, base, D, work, nwork);
-      return launch_dyn(kb_c2r_nl_cnx<T, MODE_OBSERVE, CLS, S>, grid, lds, st, base, D, work, nwork);
-    case BP_CN:
-      if (mode == MODE_IMAG)
-        return launch_dyn(kb_cn_y<T, MODE_IMAG, CLS, S>, grid, lds, st, base, D, work, nwork);
-      return launch_dyn(kb_cn_y<T, MODE_REAL, CLS, S>, grid, lds, st, base, D, work, nwork);
-    default:
-      return hipErrorInvalidValue;
-  }
+static hipError_t launch_items(const void* kern, int grid, size_t lds, hipStream_t st, char* base,
+                               const BDesc<T>* D, const WorkItem* work1, int n1,
+                               const WorkItem* work0) {
+  void* args[] = {&base, &D, &work1, &n1, &work0};
+  return hipLaunchKernel(kern, dim3(grid), dim3(kThreads), args, lds, st);
 }
 
 template <>
@@ -157,11 +140,20 @@ hipError_t batch_launch<T>(int pass, int mode, int cls, int shape, int grid, siz
                            hipStream_t st, char* base, const BDesc<T>* D, const WorkItem* work,
                            int nwork) {
   if (grid <= 0 || nwork <= 0) return hipSuccess;
-  if (cls == 0)
-    return shape == 0 ? launch_class<0, 0>(pass, mode, grid, lds, st, base, D, work, nwork)
-                      : launch_class<0, 1>(pass, mode, grid, lds, st, base, D, work, nwork);
-  return shape == 0 ? launch_class<1, 0>(pass, mode, grid, lds, st, base, D, work, nwork)
-                    : launch_class<1, 1>(pass, mode, grid, lds, st, base, D, work, nwork);
+  if (grid >= nwork)
+    return launch_items(item_kernel(pass, mode, cls, shape), nwork, lds, st, base, D, work, nwork,
+                        nullptr);
+  void* args[] = {&base, &D, &work, &nwork};
+  return hipLaunchKernel(batch_loop_kernel<T>(pass, mode, cls, shape), dim3(grid), dim3(kThreads),
+                         args, lds, st);
+}
+
+template <>
+hipError_t batch_launch_both<T>(int pass, int mode, size_t lds, hipStream_t st, char* base,
+                                const BDesc<T>* D, const WorkItem* work1, int n1,
+                                const WorkItem* work0, int n0) {
+  return launch_items(item_kernel(pass, mode, kBatchBoth, 0), n1 + n0, lds, st, base, D, work1, n1,
+                      work0);
 }
 
 template <>

@@ -25,7 +25,7 @@ struct FinArgs {
   double* ring;
   int* ring_pos;
   int ring_cap;
-  double* obs;         // FIN_OBSERVE output record
+  double* obs;         // FIN_OBSERVE output: the record, then the flags (one copy to the host)
   double* stage;       // two-stage reduction: kStageVals doubles per pre-reduced slice
   int nstage;          // slices (0: the finalize block reads the partials directly)
 };
@@ -152,7 +152,10 @@ __device__ inline void finalize_block(const FinArgs& a, int mode) {
 #pragma unroll
   for (int k = 0; k < kRecord; ++k) dst[k] = rec[k];
   if (!isfinite(norm)) *a.flags |= 1;
-  if (mode == FIN_OBSERVE) return;
+  if (mode == FIN_OBSERVE) {
+    a.obs[kRecord] = (double)*a.flags;
+    return;
+  }
   // new state: imaginary time renormalises, real time keeps the physical values
   const double nout = v[9] * dV;
   // imaginary time must renormalise (a zero state cannot be); real time only needs the

@@ -52,3 +52,32 @@ def test_launch_forms_agree_bitwise(prec, sizes, imag):
         for x, y in zip(ref, got):
             assert np.all(np.isfinite(x)) and np.array_equal(x, y)
         assert str(href) == str(hgot)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-12), ("fp32", 1e-6)])
+def test_energies_of_all_instances(prec, tol):
+    """The records of one batch call against each instance's own (same terms and sums;
+    multiply-adds may be contracted differently), after steps and with a changed coupling;
+    an instance without a state, or with a state that is not finite, is an error."""
+    from paper_1601_04640_amd.binding import Batch, GPError, gp_energy, gp_set_couplings
+    sizes = SETS["both"]
+    b = Batch([_params(n0, n1, i) for i, (n0, n1) in enumerate(sizes)], prec=prec)
+    rng = np.random.default_rng(11)
+    psi = [rng.standard_normal(s + (2,)) @ np.array([1.0, 1j]) for s in b.shapes]
+    for i, z in enumerate(psi[:-1]):
+        b.set_psi(i, z / np.sqrt((np.abs(z) ** 2).sum() * 0.01))
+    with pytest.raises(GPError):
+        b.energy()
+    b.set_psi(b.count - 1, psi[-1])
+    b.step_real(2)
+    gp_set_couplings(b.ctxs[1], 3.0, 1.0)
+    for got, ctx in zip(b.energy(), b.ctxs):
+        ref = gp_energy(ctx)
+        for key in ref:
+            assert np.allclose(got[key], ref[key], rtol=tol, atol=tol * abs(ref["energy"])), key
+    bad = psi[2].copy()
+    bad[3, 5] = np.nan
+    b.set_psi(2, bad)
+    with pytest.raises(GPError):
+        b.energy()
+    b.close()

@@ -579,22 +579,32 @@ struct Passes {
     return pass_end(c, GP_PASS_CONV_Y);
   }
 
-  static gp_status g_convolution(gp_ctx* c, const cpx<T>* src, const double* scale) {
+  // fin: a folded finalisation of the step before (null: none), of which the x pass carries
+  // the only stage, or the first of two and the forward y lines the second
+  static gp_status g_convolution(gp_ctx* c, const cpx<T>* src, const double* scale,
+                                 const FinArgs* fin = nullptr, int fin_mode = 0) {
     const Layout& L = c->L;
     const int H = L.n0 / 2 + 1;
+    FoldedFin f0{}, f1{};
+    if (fin) {
+      const int nb = fin->nstage > 0 ? fin->nstage : 1;
+      f0 = FoldedFin{*fin, fin_mode, fin->nstage > 0, nb, (nb + kXcds - 1) / kXcds * kXcds};
+      if (fin->nstage > 0) f1 = FoldedFin{*fin, fin_mode, 0, 1, kXcds};
+    }
+    double* px = c->at<double>(L.o_px[c->px_sel]);
     if (L.lx) {
       GP_PASS(c, GP_PASS_R2C_X,
               GLaunch<T>::lx_r2c(c->st, src, gscr(c), spec(c), L.lxg, c->lplan[0][0],
                                  c->lplan[0][1], ltw(c, 0, 0), ltw(c, 0, 1), ltw(c, 0, 2),
-                                 c->at<double>(L.o_px[0])));
+                                 px));
     } else if (L.ra[0].k) {
       GP_PASS(c, GP_PASS_R2C_X,
               RLaunch<T>::r2c(c->st, L.xr, L.ra[0], src, spec(c), rprog(c, 0, RL_FWD),
-                              c->at<double>(L.o_px[0])));
+                              px, f0));
     } else {
       GP_PASS(c, GP_PASS_R2C_X,
               GLaunch<T>::r2c_x(c->st, src, spec(c), c->gplan[0], tw(c, 0),
-                                c->at<double>(L.o_px[0]), L.n0, L.n1, L.n2));
+                                px, L.n0, L.n1, L.n2));
     }
     if (L.lx || L.ly) return g_conv_y_long(c, scale);
     const GKtab none{0, L.n1, L.n2, fdiv_make((uint32_t)L.n1)};
@@ -603,7 +613,7 @@ struct Passes {
       // y lines l = kx n2 + k2 (contiguous); z lines l = kx n1 + k1 (stride n1)
       GP_PASS(c, GP_PASS_FFT_Y_FWD,
               r1 ? RLaunch<T>::contiguous(c->st, spec(c), H * L.n2, L.ra[1], rprog(c, 1, RL_FWD),
-                                          nullptr, nullptr)
+                                          nullptr, nullptr, f1)
                  : GLaunch<T>::lines(GL_FWD, c->st, spec(c), L.n1, H * L.n2, 1, L.n1, 0, 1,
                                 c->gplan[1], tw(c, 1), nullptr, none, scale));
       GP_PASS(c, GP_PASS_CONV_Z,
@@ -614,13 +624,13 @@ struct Passes {
                                 Kp(c), GKtab{1, L.n1, L.n2, fdiv_make((uint32_t)L.n1)}, scale));
       GP_PASS(c, GP_PASS_FFT_Y_INV,
               r1 ? RLaunch<T>::contiguous(c->st, spec(c), H * L.n2, L.ra[1], rprog(c, 1, RL_INV),
-                                          nullptr, nullptr)
+                                          nullptr, nullptr, FoldedFin{})
                  : GLaunch<T>::lines(GL_INV, c->st, spec(c), L.n1, H * L.n2, 1, L.n1, 0, 1,
                                 c->gplan[1], tw(c, 1), nullptr, none, scale));
     } else {
       GP_PASS(c, GP_PASS_CONV_Y,
               r1 ? RLaunch<T>::contiguous(c->st, spec(c), H, L.ra[1], rprog(c, 1, RL_CONV), Kp(c),
-                                          scale)
+                                          scale, FoldedFin{})
                  : GLaunch<T>::lines(GL_CONV, c->st, spec(c), L.n1, H, 1, L.n1, 0, 1, c->gplan[1],
                                 tw(c, 1), Kp(c), GKtab{0, L.n1, 1, fdiv_make((uint32_t)L.n1)},
                                 scale));
@@ -702,13 +712,31 @@ struct Passes {
                                     plane, f, pc, dscr));
   }
 
+  // Whether the passes can carry the finalisation of the step before: an x pass that takes
+  // it, and for two stages y lines that run before the convolution reads the scale.
+  static bool g_folds(const gp_ctx* c) {
+    const Layout& L = c->L;
+    return L.ra[0].k && (fin_args(c, 0).nstage == 0 || (c->p.geom == GP_3D && L.ra[1].k));
+  }
+
   static gp_status g_step(gp_ctx* c, bool imag) {
     const Layout& L = c->L;
     const int mode = imag ? MODE_IMAG : MODE_REAL;
     const int k = imag ? 0 : 1;
     T* phi = c->at<T>(L.o_sfield);
+    const int fin = imag ? (int)FIN_IMAG : (int)FIN_REAL;
+    // the finalisation deferred into the next step's passes, as on specialised lengths (step)
+    const bool defer = c->tmask == 0 && g_folds(c);
+    FinArgs prev{};
+    const int prev_mode = c->pend_mode;
+    const bool fold = defer && c->fin_pending;
+    if (fold) {
+      prev = fin_args(c, c->pend_sel);
+      c->fin_pending = false;
+      c->px_sel = 1 - c->pend_sel;
+    }
     GP_TRY(settle(c));
-    GP_TRY(g_convolution(c, psi(c), &c->sc()->scale));
+    GP_TRY(g_convolution(c, psi(c), &c->sc()->scale, fold ? &prev : nullptr, prev_mode));
     GP_TRY(pass_begin(c, GP_PASS_C2R_NL_CNX));
     if (!L.ra[0].k) GP_TRY(g_c2r(c, phi));
     if (L.ra[0].k) {
@@ -739,7 +767,13 @@ struct Passes {
       GP_TRY(g_sweep(c, 1, k, 1));
       GP_TRY(pass_end(c, GP_PASS_CN_Y));
     }
-    return finalize(c, imag ? (int)FIN_IMAG : (int)FIN_REAL);
+    if (defer) {
+      c->fin_pending = true;
+      c->pend_sel = c->px_sel;
+      c->pend_mode = fin;
+      return GP_OK;
+    }
+    return finalize(c, fin);
   }
 
   static gp_status g_observe(gp_ctx* c) {

@@ -38,9 +38,8 @@ constexpr int kStageMax = 256;   // slices of the two-stage reduction (<= kThrea
 // array, then adds them, so a small step's partials arrive in one memory round trip
 // (U = 4; U = 1 inside a pass kernel, to stay within the pass's register budget).
 template <int U = 4>
-__device__ inline void fin_gather(const FinArgs& a, int mode, int slice, int nslice,
+__device__ inline void fin_gather(const FinArgs& a, int mode, int slice, int nslice, int tid,
                                   double (&v)[11]) {
-  const int tid = threadIdx.x;
   const bool xnl = mode != FIN_EKZ;
   const bool col = mode != FIN_OBSERVE || a.geom == 0;
   auto lo_of = [&](int nb) { return (int)((long long)nb * slice / nslice); };
@@ -69,15 +68,50 @@ __device__ inline void fin_gather(const FinArgs& a, int mode, int slice, int nsl
   }
 }
 
-// First stage of the two-stage reduction: block g writes the totals of slice g.
-template <int U = 4>
-__device__ inline void prereduce_block(const FinArgs& a, int mode, int g) {
-  __shared__ double red[11 * kWaves];
-  double v[11];
+// Totals, in thread 0, of slice `slice` of `nslice` (or, nslice = 0, of the pre-reduced
+// slices), summed as kThreads threads in kThreads / 64 waves.  ANY: the block has any number
+// of whole waves and each takes its share of those (same sums, bit for bit).  red: LDS for
+// 11 kWaves doubles.
+template <int U, bool ANY>
+__device__ inline void fin_totals(const FinArgs& a, int mode, int slice, int nslice,
+                                  double (&v)[11], double* red) {
+  const int lane = threadIdx.x & 63;
+  const int nw = ANY ? min((int)blockDim.x >> 6, kWaves) : kWaves;
+  for (int w = threadIdx.x >> 6; w < kWaves; w += nw) {
+    const int tid = w * 64 + lane;
 #pragma unroll
-  for (int k = 0; k < 11; ++k) v[k] = 0.0;
-  fin_gather<U>(a, mode, g, a.nstage, v);
-  block_sum<11>(v, red);
+    for (int k = 0; k < 11; ++k) v[k] = 0.0;
+    if (nslice > 0) {
+      fin_gather<U>(a, mode, slice, nslice, tid, v);
+    } else if (tid < a.nstage) {  // one slice per thread (nstage <= kStageMax <= kThreads)
+#pragma unroll
+      for (int k = 0; k < kStageVals; ++k) v[k] = a.stage[tid * kStageVals + k];
+    }
+#pragma unroll
+    for (int k = 0; k < 11; ++k) v[k] = wave_sum_to_last(v[k]);
+    if (lane == 63) {
+#pragma unroll
+      for (int k = 0; k < 11; ++k) red[k * kWaves + w] = v[k];
+    }
+    if (!ANY) break;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < 11; ++k) {
+      double acc = red[k * kWaves];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) acc += red[k * kWaves + w];
+      v[k] = acc;
+    }
+  }
+}
+
+// First stage of the two-stage reduction: block g writes the totals of slice g.
+template <int U, bool ANY>
+__device__ inline void prereduce_waves(const FinArgs& a, int mode, int g, double* red) {
+  double v[11];
+  fin_totals<U, ANY>(a, mode, g, a.nstage, v, red);
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int k = 0; k < kStageVals; ++k) a.stage[g * kStageVals + k] = v[k];
@@ -85,16 +119,13 @@ __device__ inline void prereduce_block(const FinArgs& a, int mode, int g) {
 }
 
 // All threads of one block must call this.
-template <int U = 4>
-__device__ inline void finalize_block(const FinArgs& a, int mode) {
+template <int U, bool ANY>
+__device__ inline void finalize_waves(const FinArgs& a, int mode, double* red) {
   // no multiply-add contraction: the record rounds the same wherever this is inlined (its
   // own kernel, or folded into a pass kernel)
 #pragma clang fp contract(off)
-  __shared__ double red[11 * kWaves];
   const int tid = threadIdx.x;
   double v[11];
-#pragma unroll
-  for (int k = 0; k < 11; ++k) v[k] = 0.0;
   // the scalars thread 0 needs at the end are fetched before the gather
   double s = 1.0, ekz_in = 0.0;
   int pos = 0;
@@ -103,17 +134,7 @@ __device__ inline void finalize_block(const FinArgs& a, int mode) {
     if (mode != FIN_EKZ && mode != FIN_OBSERVE && a.geom == 0) ekz_in = *a.ekz;
     if (mode != FIN_EKZ && mode != FIN_OBSERVE) pos = *a.ring_pos;
   }
-  if (a.nstage > 0) {
-    // one pre-reduced slice per thread (nstage <= kStageMax < kThreads), then the
-    // fixed-order block sum
-    if (tid < a.nstage) {
-#pragma unroll
-      for (int k = 0; k < kStageVals; ++k) v[k] = a.stage[tid * kStageVals + k];
-    }
-  } else {
-    fin_gather<U>(a, mode, 0, 1, v);
-  }
-  block_sum<11>(v, red);
+  fin_totals<U, ANY>(a, mode, 0, a.nstage > 0 ? 0 : 1, v, red);
   if (tid != 0) return;
   const double s2 = s * s;
   if (mode == FIN_EKZ) {
@@ -168,6 +189,38 @@ __device__ inline void finalize_block(const FinArgs& a, int mode) {
   const double sn = (mode == FIN_IMAG) ? 1.0 / sqrt(nout) : 1.0;
   *a.scale = sn;
   if (a.geom == 0) *a.ekz = 0.5 * sn * sn * v[10] / (a.h2 * a.h2) * dV;
+}
+
+// The same for blocks of kThreads threads.
+template <int U = 4>
+__device__ inline void prereduce_block(const FinArgs& a, int mode, int g) {
+  __shared__ double red[11 * kWaves];
+  prereduce_waves<U, false>(a, mode, g, red);
+}
+template <int U = 4>
+__device__ inline void finalize_block(const FinArgs& a, int mode) {
+  __shared__ double red[11 * kWaves];
+  finalize_waves<U, false>(a, mode, red);
+}
+
+// A finalisation folded into a pass kernel of any block size: `lead` leading blocks (a
+// multiple of the XCDs, so that the tiles keep theirs), of which the first `blocks` work.
+// stage: 1, the pre-reduction of a two-stage one; 0, the finalisation itself.
+struct FoldedFin {
+  FinArgs a;
+  int mode, stage, blocks, lead;
+};
+// True if this is a leading block (its work is done).  lds: kFoldedLds bytes.
+constexpr size_t kFoldedLds = 11 * kWaves * sizeof(double);
+__device__ inline bool folded_fin(const FoldedFin& f, char* lds) {
+  const int b = blockIdx.x;
+  if (b >= f.lead) return false;
+  if (b < f.blocks) {
+    double* red = reinterpret_cast<double*>(lds);
+    if (f.stage) prereduce_waves<1, true>(f.a, f.mode, b, red);
+    else finalize_waves<1, true>(f.a, f.mode, red);
+  }
+  return true;
 }
 
 }  // namespace gpdbec

@@ -529,16 +529,21 @@ template <typename T, int NLC, int MAXR>
 __global__ void __launch_bounds__(r_max_threads<T>()) k_rlines(cpx<T>* __restrict__ data, RLines g,
                                                       const RProgram* __restrict__ p,
                                                       const T* __restrict__ ktab,
-                                                      const double* __restrict__ scale) {
+                                                      const double* __restrict__ scale,
+                                                      FoldedFin fin) {
   constexpr unsigned CB = sizeof(cpx<T>);
   extern __shared__ __align__(16) char rfft_raw[];
+  if constexpr (NLC == 0) {  // the forward y lines may carry a finalisation's second stage
+    if (folded_fin(fin, rfft_raw)) return;
+  }
   const int n = p->n, m = p->m;
   const RTile<NLC> tile{g.nl, g.ls};
   cpx<T>* tw = reinterpret_cast<cpx<T>*>(rfft_raw);
   cpx<T>* buf = tw + m;
   T* kt = reinterpret_cast<T*>(buf + (NLC > 0 ? m * NLC : g.nl * g.ls));
   // tiles numbered XCD-contiguously: neighbours share 128-byte lines and an L2
-  const int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int lead = NLC == 0 ? fin.lead : 0;
+  const int b = xcd_tile(blockIdx.x - lead, gridDim.x - lead);
   int plane = 0, l0;
   cpx<T>* base;
   unsigned bytes, step;

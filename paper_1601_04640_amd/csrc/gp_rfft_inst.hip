@@ -111,27 +111,30 @@ namespace {
 template <int NLC>
 hipError_t launch(hipStream_t st, int blocks, int threads, size_t lds, cpx<T>* data,
                   const RLines& g, int maxr, const RProgram* p, const T* ktab,
-                  const double* scale) {
+                  const double* scale, const FoldedFin& fin = {}) {
+  blocks += fin.lead;
+  if (lds < kFoldedLds) lds = kFoldedLds;
   if (maxr == kSmall)
     hipLaunchKernelGGL((k_rlines<T, NLC, kSmall>), dim3(blocks), dim3(threads), lds, st, data, g,
-                       p, ktab, scale);
+                       p, ktab, scale, fin);
   else
     hipLaunchKernelGGL((k_rlines<T, NLC, kBig>), dim3(blocks), dim3(threads), lds, st, data, g, p,
-                       ktab, scale);
+                       ktab, scale, fin);
   return hipGetLastError();
 }
 }  // namespace
 
 template <>
 hipError_t RLaunch<T>::contiguous(hipStream_t st, cpx<T>* data, int nlines, const RAxis& a,
-                                  const RProgram* p, const T* ktab, const double* scale) {
+                                  const RProgram* p, const T* ktab, const double* scale,
+                                  const FoldedFin& fin) {
   if (!contiguous_ok(a) || nlines < 1) return hipErrorInvalidValue;
   const int nl = contiguous_lines(a, nlines);
   const RLines g{nlines, nl, r_line_slots(a.m), 0, 1u, 0};
   const int blocks = (nlines + nl - 1) / nl;
   return launch<0>(st, blocks, r_spread<T>(a, nl, r_threads<T>(a, nl, false), blocks),
                    lds_contiguous(a, nl, ktab != nullptr), data,
-                   g, a.maxr, p, ktab, scale);
+                   g, a.maxr, p, ktab, scale, fin);
 }
 
 template <>
@@ -222,6 +225,7 @@ RXCfg RLaunch<T>::x_r2c(const RAxis& a, int n1, int n2) {
                             (long long)c.xt.nbj * n2);
     const size_t lines = sizeof(cpx<T>) * (size_t)c.xt.np * c.xt.ls;
     c.lds = sizeof(cpx<T>) * (size_t)a.m + (lines < 256 ? 256 : lines);
+    if (c.lds < kFoldedLds) c.lds = kFoldedLds;
   });
 }
 
@@ -256,14 +260,14 @@ RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
 
 template <>
 hipError_t RLaunch<T>::r2c(hipStream_t st, const RXCfg& c, const RAxis& a, const cpx<T>* psi,
-                           cpx<T>* spec, const RProgram* p, double* part) {
+                           cpx<T>* spec, const RProgram* p, double* part, const FoldedFin& fin) {
   if (c.blocks < 1) return hipErrorInvalidValue;
   if (a.maxr == kSmall)
-    hipLaunchKernelGGL((k_rr2c<T, kSmall>), dim3(c.blocks), dim3(c.threads), c.lds, st, psi, spec,
-                       c.xt, p, part);
+    hipLaunchKernelGGL((k_rr2c<T, kSmall>), dim3(c.blocks + fin.lead), dim3(c.threads), c.lds, st,
+                       psi, spec, c.xt, p, part, fin);
   else
-    hipLaunchKernelGGL((k_rr2c<T, kBig>), dim3(c.blocks), dim3(c.threads), c.lds, st, psi, spec,
-                       c.xt, p, part);
+    hipLaunchKernelGGL((k_rr2c<T, kBig>), dim3(c.blocks + fin.lead), dim3(c.threads), c.lds, st,
+                       psi, spec, c.xt, p, part, fin);
   return hipGetLastError();
 }
 

@@ -43,12 +43,13 @@ struct RLaunch {
   static RXCfg x_r2c(const RAxis& a, int n1, int n2);
   static RXCfg x_c2r(const RAxis& a, int n1, int n2);
   static hipError_t r2c(hipStream_t st, const RXCfg& c, const RAxis& a, const cpx<T>* psi,
-                        cpx<T>* spec, const RProgram* p, double* part);
+                        cpx<T>* spec, const RProgram* p, double* part, const FoldedFin& fin);
   static hipError_t c2r(hipStream_t st, const RXCfg& c, const RAxis& a, int mode,
                         const cpx<T>* spec, const RProgram* p, const RXArgs<T>& g);
   // contiguous lines of a.n points (nlines of them); scale, ktab: the convolution's
   static hipError_t contiguous(hipStream_t st, cpx<T>* data, int nlines, const RAxis& a,
-                               const RProgram* p, const T* ktab, const double* scale);
+                               const RProgram* p, const T* ktab, const double* scale,
+                               const FoldedFin& fin);
   // lines at stride cols in `planes` planes of a.n x cols values (convolution: the 3D
   // quadrant table)
   static hipError_t strided(hipStream_t st, cpx<T>* data, int cols, int planes, const RAxis& a,
@@ -63,12 +64,14 @@ struct RLaunch {
   template <> RXCfg RLaunch<T>::x_r2c(const RAxis&, int, int);                                 \
   template <> RXCfg RLaunch<T>::x_c2r(const RAxis&, int, int);                                 \
   template <> hipError_t RLaunch<T>::r2c(hipStream_t, const RXCfg&, const RAxis&,              \
-                                         const cpx<T>*, cpx<T>*, const RProgram*, double*);    \
+                                         const cpx<T>*, cpx<T>*, const RProgram*, double*,     \
+                                         const FoldedFin&);                                    \
   template <> hipError_t RLaunch<T>::c2r(hipStream_t, const RXCfg&, const RAxis&, int,         \
                                          const cpx<T>*, const RProgram*, const RXArgs<T>&);    \
   template <> bool RLaunch<T>::strided_ok(const RAxis&, int);                                  \
   template <> hipError_t RLaunch<T>::contiguous(hipStream_t, cpx<T>*, int, const RAxis&,       \
-                                                const RProgram*, const T*, const double*);     \
+                                                const RProgram*, const T*, const double*,      \
+                                                const FoldedFin&);                             \
   template <> hipError_t RLaunch<T>::strided(hipStream_t, cpx<T>*, int, int, const RAxis&,     \
                                              const RProgram*, const T*, const double*);
 GP_DECLARE_RFFT(float)

@@ -46,18 +46,23 @@ __device__ __forceinline__ void rx_block_store(double (&v)[NV], double* red,
 // B_k = (Z_k - conj Z_(N-k))/(2i).  part[2b], part[2b+1]: sums of |psi_(i+1) - psi_i|^2 of
 // the stored state along x and along axis 1 (from the block's lines to their successors).
 // The x neighbour comes from the next lane (the last lane of a wave loads its own).
+// fin: the finalisation of the step before (or its first stage), which nothing in this pass
+// waits for, in leading blocks (540x600 FP64: 51.7 us a step with a kernel of its own, 48.2
+// so; this pass 10.4 and 10.9).
 template <typename T, int MAXR>
 __global__ void __launch_bounds__(r_max_threads<T>()) k_rr2c(const cpx<T>* __restrict__ psi,
                                                     cpx<T>* __restrict__ spec, RXTile xt,
                                                     const RProgram* __restrict__ p,
-                                                    double* __restrict__ part) {
+                                                    double* __restrict__ part, FoldedFin fin) {
   constexpr unsigned CB = sizeof(cpx<T>);
   constexpr int U = sizeof(T) == 4 ? 4 : 2;  // points of a pair per thread and round
   extern __shared__ __align__(16) char rx_raw[];
+  if (folded_fin(fin, rx_raw)) return;
+  const int bid = blockIdx.x - fin.lead;
   const int N = xt.n0, n1 = xt.n1, m = p->m, nt = blockDim.x;
   cpx<T>* tw = reinterpret_cast<cpx<T>*>(rx_raw);
   cpx<T>* buf = tw + m;
-  const int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int b = xcd_tile(bid, gridDim.x - fin.lead);
   const int k = b / xt.nbj, j0 = (b - k * xt.nbj) * 2 * xt.np;
   const int lines = min(2 * xt.np, n1 - j0), npairs = (lines + 1) / 2;
   const RTile<0> tile{npairs, xt.ls};
@@ -130,7 +135,7 @@ __global__ void __launch_bounds__(r_max_threads<T>()) k_rr2c(const cpx<T>* __res
     }
   }
   __syncthreads();  // the line buffer is free: it holds the reduction
-  rx_block_store<2>(s, reinterpret_cast<double*>(buf), part + 2 * (long long)blockIdx.x);
+  rx_block_store<2>(s, reinterpret_cast<double*>(buf), part + 2 * (long long)bid);
 }
 
 // What the complex-to-real pass works on: psi, V, the scale of psi, the x factors and their

@@ -203,17 +203,18 @@ Layout make_layout(const gp_params* p, unsigned host = 0, bool batch = false) {
   L.sy = L.sy || L.ly;
   // y lines are contiguous in the spectrum, z lines strided (no long axis: those split)
   if (L.generic && !L.lx && !L.ly) {
-    const RAxis a0 = fp64 ? r_axis<double>(L.n0) : r_axis<float>(L.n0);
+    const long long np = (long long)L.n0 * L.n1 * L.n2;
+    const RAxis a0 = fp64 ? r_axis<double>(L.n0, np) : r_axis<float>(L.n0, np);
     L.xr = fp64 ? RLaunch<double>::x_r2c(a0, L.n1, L.n2) : RLaunch<float>::x_r2c(a0, L.n1, L.n2);
     L.xc = fp64 ? RLaunch<double>::x_c2r(a0, L.n1, L.n2) : RLaunch<float>::x_c2r(a0, L.n1, L.n2);
     if (L.xr.blocks && L.xc.blocks) {
       L.ra[0] = a0;
       L.sw[0] = L.xc.sweep();
     }
-    RAxis a1 = fp64 ? r_axis<double>(L.n1) : r_axis<float>(L.n1);
+    RAxis a1 = fp64 ? r_axis<double>(L.n1, np) : r_axis<float>(L.n1, np);
     if (fp64 ? RLaunch<double>::contiguous_ok(a1) : RLaunch<float>::contiguous_ok(a1)) L.ra[1] = a1;
     if (p->geom == GP_3D) {
-      RAxis a2 = fp64 ? r_axis<double>(L.n2) : r_axis<float>(L.n2);
+      RAxis a2 = fp64 ? r_axis<double>(L.n2, 0) : r_axis<float>(L.n2, 0);
       if (fp64 ? RLaunch<double>::strided_ok(a2, L.n1) : RLaunch<float>::strided_ok(a2, L.n1))
         L.ra[2] = a2;
     }

@@ -22,6 +22,9 @@ GRIDS = [
     (26, 15, 18), (37, 18, 20), (63, 17, 18), (77, 34, 15), (100, 9, 18), (121, 18, 7), (169, 18, 9),
     (225, 33, 8), (397, 18, 10), (600, 21, 9), (1024, 18, 1), (1331, 21, 1), (2000, 19, 1),
     (1999, 18, 1), (144, 130, 70),
+    # grids of a range that takes radices up to 8
+    (36, 32, 30), (60, 50, 40), (63, 45, 20), (100, 81, 18), (225, 210, 1), (540, 600, 1),
+    (700, 720, 1),
 ]
 
 

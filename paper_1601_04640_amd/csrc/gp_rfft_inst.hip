@@ -223,6 +223,9 @@ RXCfg RLaunch<T>::x_r2c(const RAxis& a, int n1, int n2) {
   return x_shape(a, n1, n2, [&](RXCfg& c) {
     c.threads = r_spread<T>(a, c.xt.np, r_threads<T>(a, c.xt.np, false),
                             (long long)c.xt.nbj * n2);
+    // five blocks of 256 threads share a CU where two of 512 do (85 VGPRs): 400^3 FP32 in
+    // 64-byte runs 257 us, 279 in 128-byte ones
+    if (F32 && c.xt.np == kWide / 2 && c.threads > 256) c.threads = 1 << 20;  // no such shape
     const size_t lines = sizeof(cpx<T>) * (size_t)c.xt.np * c.xt.ls;
     c.lds = sizeof(cpx<T>) * (size_t)a.m + (lines < 256 ? 256 : lines);
     if (c.lds < kFoldedLds) c.lds = kFoldedLds;

@@ -244,6 +244,7 @@ RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
       c.xt.P = sweep / tl;
       c.threads = sweep > fft ? sweep : fft;
       if (c.threads > most) c.threads = 1 << 20;  // no such shape
+      if (rows == 16 && c.xt.np == kWide / 2 && c.threads > 256) c.threads = 1 << 20;
       const size_t v = (size_t)a.m + (size_t)tl * c.xt.ls + 2 * (size_t)(sweep / 64) * tl +
                        (size_t)c.xt.P * (rows + kSweepGains);
       c.lds = sizeof(cpx<T>) * v;
@@ -251,9 +252,10 @@ RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
       if (c.lds < least) c.lds = least;
     });
   };
-  // FP32 grids that fill the GPU sweep in chunks of 16 rows, so that a block of 512 threads
-  // takes 16 lines and two share a CU (400^3: 477 us, 696 with 8 rows); smaller ones in
-  // shorter chains of 8 (101x75x63: 20.0 us against 21.6).
+  // FP32 grids that fill the GPU sweep in chunks of 16 rows, 16 lines in a block of up to 256
+  // threads or else 8, so that four or more blocks share a CU (a step of 400^3: 1524 us, 1541
+  // with 16 lines in 512 threads; 390x90x90: 116.5 us, 130.1 with 8 rows); smaller ones in
+  // shorter chains of 8 (101x75x63: 20.0 us against 21.6 for this pass).
   if (F32) {
     const RXCfg c = with(16, 512);
     if (c.blocks >= 1024) return c;

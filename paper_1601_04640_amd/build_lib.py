@@ -39,10 +39,7 @@ def _jobs(build_dir=BUILD, extra=()):
     for real in ("float", "double"):
         for kind in ("batch", "batch_loop"):
             obj = os.path.join(build_dir, f"{kind}_{real}.o")
-            # multiply-adds contracted within an expression only, so that the two forms of
-            # a pass, compiled apart, round the same
-            jobs.append((obj, [HIPCC, *FLAGS, *extra, "-ffp-contract=on",
-                               f"-DGP_REAL={real}", "-c",
+            jobs.append((obj, [HIPCC, *FLAGS, *extra, f"-DGP_REAL={real}", "-c",
                                os.path.join(CSRC, f"gp_{kind}_inst.hip"), "-o", obj]))
     for real in ("float", "double"):
         obj = os.path.join(build_dir, f"sweep_{real}.o")

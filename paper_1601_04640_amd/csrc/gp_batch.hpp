@@ -54,19 +54,19 @@ __host__ __device__ constexpr int batch_class(int n) { return n > 256 ? 1 : 0; }
 // Dynamic LDS: the largest body of the pass and class present is requested at launch.
 //
 // What bounds these kernels is how many waves a SIMD holds while each tile's load, LDS
-// transform and store wait on each other, so registers decide.  One block per work item
-// (GP_ITEM_LOOP_KERNELS not defined; the default) leaves nothing alive across items and
-// balances the load by dispatch: against persistent blocks that walk the list, the
-// class-1 c2r takes 147 instead of 200 VGPRs and the class-1 CN 140 instead of 201 (three
-// waves per SIMD instead of two), the class-0 CN 101 instead of 134, and 192 FP32
-// instances of 96^2 to 512^2 points (13.7 M) step in 0.262 ms instead of 0.317.  The
-// persistent form (gp_batch_set_blocks below the item count) walks items
-// blockIdx.x + k gridDim.x of the list.
+// transform and store wait on each other, so registers decide.  c2r and CN take one block
+// per work item by default (GP_ITEM_LOOP_KERNELS not defined): nothing stays alive across
+// items, the class-1 c2r takes 147 instead of 200 VGPRs, the class-1 CN 140 instead of 201
+// (three waves per SIMD instead of two), the class-0 CN 101 instead of 134.  r2c and conv
+// walk items blockIdx.x + k gridDim.x with any number of blocks, as the others do when
+// gp_batch_set_blocks asks for fewer blocks than items; by default each block has one item,
+// so that dispatch balances the load.
 //
-// Class kBatchBoth covers both classes' lists in one launch, the longer lines first:
-// their bodies need the same registers anyway (c2r 134 and 147, r2c 128 and 134 VGPRs)
-// and each pass has one drained tail instead of two (with the pairing of batch_pair_xcds,
-// 0.262 -> 0.226 ms; 16 instances 0.087 -> 0.053 ms).
+// Class kBatchBoth covers both classes' lists in one launch, the longer lines first: their
+// bodies need about the same registers (c2r 134 and 147) and each pass has one drained tail
+// instead of two.  192 FP32 instances of 96^2 to 512^2 points (13.7 M) step in 0.230 ms,
+// with 1024 persistent blocks per class and pass in 0.317 (60 instances 0.093 and 0.133, 16
+// 0.053 and 0.091; 90 FP64 ones 0.271 and 0.300).
 #define GP_CLASS_BODY(AXIS, BODY)                                                      \
   if constexpr (CLS == 0) {                                                            \
     switch (d.AXIS) { GP_BATCH_CLASS0(BODY) default: break; }                          \
@@ -75,28 +75,29 @@ __host__ __device__ constexpr int batch_class(int n) { return n > 256 ? 1 : 0; }
   } else {                                                                             \
     switch (d.AXIS) { GP_BATCH_CLASS1(BODY) GP_BATCH_CLASS0(BODY) default: break; }    \
   }
+// r2c is held to three waves per SIMD in FP32 (168 VGPRs) and two in FP64 (256, four
+// spilled: 90 instances 0.271 ms a step, 0.294 with one).
+template <typename T>
+constexpr int r2c_waves() { return sizeof(T) == 4 ? 3 : 2; }
 #ifdef GP_ITEM_LOOP_KERNELS
 #define GP_BATCH_KERNEL(NAME, AXIS, BODY, WPE)                                         \
   template <typename T, int MODE, int CLS, int S>                                      \
-  __global__ __launch_bounds__(kThreads) void NAME##_loop(                             \
+  __global__ __launch_bounds__(kThreads, WPE) void NAME##_loop(                        \
       char* __restrict__ base, const BDesc<T>* __restrict__ D,                         \
-      const WorkItem* __restrict__ work, int nwork) {                                  \
+      const WorkItem* __restrict__ work1, int n1, const WorkItem* __restrict__ work0,  \
+      int nwork) {                                                                     \
     extern __shared__ __attribute__((aligned(16))) char lds[];                         \
     constexpr int K = (MODE == MODE_REAL) ? 1 : 0;                                     \
     (void)K;                                                                           \
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {                              \
-      const WorkItem item = work[w];                                                   \
+      const WorkItem item = w < n1 ? work1[w] : work0[w - n1];                         \
       const BDesc<T>& d = D[item.inst];                                                \
       GP_CLASS_BODY(AXIS, BODY)                                                        \
       __syncthreads();                                                                 \
     }                                                                                  \
   }
 #else
-// Block b takes work1[b], or work0[b - n1] from n1 on.  The FP32 r2c of both classes is held
-// to four waves per SIMD (128 instead of 134 VGPRs, no spill: 46.8 -> 40.8 us); c2r and CN
-// spill there and lose (80 -> 95, 53 -> 56 us).
-template <typename T, int CLS>
-constexpr int r2c_waves() { return CLS == kBatchBoth && sizeof(T) == 4 ? 4 : 1; }
+// Block b takes work1[b], or work0[b - n1] from n1 on.
 #define GP_BATCH_KERNEL(NAME, AXIS, BODY, WPE)                                         \
   template <typename T, int MODE, int CLS, int S>                                      \
   __global__ __launch_bounds__(kThreads, WPE) void NAME(                               \
@@ -138,7 +139,7 @@ constexpr int r2c_waves() { return CLS == kBatchBoth && sizeof(T) == 4 ? 4 : 1; 
                                   bptr<double>(base, d.p_col), d.n0, (size_t)d.n0,        \
                                   (size_t)d.n0 * d.n1, item.tile, lds);                   \
     break;
-GP_BATCH_KERNEL(kb_r2c_x, n0, GP_BODY_R2C, (r2c_waves<T, CLS>()))
+GP_BATCH_KERNEL(kb_r2c_x, n0, GP_BODY_R2C, r2c_waves<T>())
 GP_BATCH_KERNEL(kb_conv_y, n1, GP_BODY_CONV, 1)
 GP_BATCH_KERNEL(kb_c2r_nl_cnx, n0, GP_BODY_C2R, 1)
 GP_BATCH_KERNEL(kb_cn_y, n1, GP_BODY_CN, 1)

@@ -1,8 +1,9 @@
-// Multi-instance kernels for one precision (GP_REAL), a block per work item, and the
-// launchers of these and of the persistent ones.
+// Multi-instance kernels for one precision (GP_REAL) that take a block per work item (c2r and
+// CN), and the launchers of these and of those that walk their list.
 #include "gp_batch.hpp"
 #include "gp_batch_launch.hpp"
 
+#include <algorithm>
 #include <mutex>
 
 #ifndef GP_REAL
@@ -85,12 +86,14 @@ int batch_tiles<T>(int pass, int n0, int n1, int shape) {
   return shape == 1 ? tiles_of_shape<1>(pass, n0, n1) : tiles_of_shape<0>(pass, n0, n1);
 }
 
-// The kernel behind (pass, mode, class, shape), as an untyped function pointer.
+// r2c and conv are one kernel for any number of blocks: their FFTs, compiled twice, would
+// round differently in the two forms (c2r and CN agree).
+static bool has_item_kernel(int pass) { return pass == BP_C2R || pass == BP_CN; }
+
+// The item kernel behind (pass, mode, class, shape), as an untyped function pointer.
 template <int CLS, int S>
 static const void* kernel_of(int pass, int mode) {
   switch (pass) {
-    case BP_R2C: return reinterpret_cast<const void*>(kb_r2c_x<T, 0, CLS, S>);
-    case BP_CONV: return reinterpret_cast<const void*>(kb_conv_y<T, 0, CLS, S>);
     case BP_C2R:
       if (mode == MODE_IMAG) return reinterpret_cast<const void*>(kb_c2r_nl_cnx<T, MODE_IMAG, CLS, S>);
       if (mode == MODE_REAL) return reinterpret_cast<const void*>(kb_c2r_nl_cnx<T, MODE_REAL, CLS, S>);
@@ -119,20 +122,25 @@ hipError_t batch_reserve_lds<T>(int pass, int mode, int cls, int shape, size_t l
   std::lock_guard<std::mutex> lock(mu);
   size_t& h = have[pass][mode][cls][shape];
   if (lds <= h) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(item_kernel(pass, mode, cls, shape),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e == hipSuccess && cls != kBatchBoth)
+  hipError_t e = hipSuccess;
+  if (has_item_kernel(pass))
+    e = hipFuncSetAttribute(item_kernel(pass, mode, cls, shape),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e == hipSuccess && (cls != kBatchBoth || !has_item_kernel(pass)))
     e = hipFuncSetAttribute(batch_loop_kernel<T>(pass, mode, cls, shape),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e == hipSuccess) h = lds;
   return e;
 }
 
-static hipError_t launch_items(const void* kern, int grid, size_t lds, hipStream_t st, char* base,
-                               const BDesc<T>* D, const WorkItem* work1, int n1,
-                               const WorkItem* work0) {
-  void* args[] = {&base, &D, &work1, &n1, &work0};
-  return hipLaunchKernel(kern, dim3(grid), dim3(kThreads), args, lds, st);
+static hipError_t launch_pass(int pass, int mode, int cls, int shape, int grid, size_t lds,
+                              hipStream_t st, char* base, const BDesc<T>* D,
+                              const WorkItem* work1, int n1, const WorkItem* work0, int nwork) {
+  void* args[] = {&base, &D, &work1, &n1, &work0, &nwork};  // (an item kernel takes no nwork)
+  const bool items = grid >= nwork && has_item_kernel(pass);
+  return hipLaunchKernel(items ? item_kernel(pass, mode, cls, shape)
+                               : batch_loop_kernel<T>(pass, mode, cls, shape),
+                         dim3(std::min(grid, nwork)), dim3(kThreads), args, lds, st);
 }
 
 template <>
@@ -140,20 +148,15 @@ hipError_t batch_launch<T>(int pass, int mode, int cls, int shape, int grid, siz
                            hipStream_t st, char* base, const BDesc<T>* D, const WorkItem* work,
                            int nwork) {
   if (grid <= 0 || nwork <= 0) return hipSuccess;
-  if (grid >= nwork)
-    return launch_items(item_kernel(pass, mode, cls, shape), nwork, lds, st, base, D, work, nwork,
-                        nullptr);
-  void* args[] = {&base, &D, &work, &nwork};
-  return hipLaunchKernel(batch_loop_kernel<T>(pass, mode, cls, shape), dim3(grid), dim3(kThreads),
-                         args, lds, st);
+  return launch_pass(pass, mode, cls, shape, grid, lds, st, base, D, work, nwork, nullptr, nwork);
 }
 
 template <>
 hipError_t batch_launch_both<T>(int pass, int mode, size_t lds, hipStream_t st, char* base,
                                 const BDesc<T>* D, const WorkItem* work1, int n1,
                                 const WorkItem* work0, int n0) {
-  return launch_items(item_kernel(pass, mode, kBatchBoth, 0), n1 + n0, lds, st, base, D, work1, n1,
-                      work0);
+  return launch_pass(pass, mode, kBatchBoth, 0, n1 + n0, lds, st, base, D, work1, n1, work0,
+                     n1 + n0);
 }
 
 template <>

@@ -29,7 +29,7 @@ hipError_t batch_launch_both(int pass, int mode, size_t lds, hipStream_t st, cha
 // kBatchBoth with shape 0: those of batch_launch_both
 template <typename T>
 hipError_t batch_reserve_lds(int pass, int mode, int cls, int shape, size_t lds);
-// the persistent kernels (compiled apart: gp_batch_loop_inst.hip)
+// The kernels that walk their list (compiled apart: gp_batch_loop_inst.hip)
 template <typename T>
 const void* batch_loop_kernel(int pass, int mode, int cls, int shape);
 template <typename T>

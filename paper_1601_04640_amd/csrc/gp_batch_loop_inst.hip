@@ -1,5 +1,5 @@
-// Persistent multi-instance kernels for one precision (GP_REAL): fewer blocks than work
-// items, each walking the list.  (Item-loop kernels: see thread_idx.)
+// Multi-instance kernels for one precision (GP_REAL) that walk their work list with any
+// number of blocks.  (Item-loop kernels: see thread_idx.)
 #define GP_ITEM_LOOP_KERNELS
 #include "gp_batch.hpp"
 #include "gp_batch_launch.hpp"
@@ -29,6 +29,9 @@ static const void* kernel_of(int pass, int mode) {
 
 template <>
 const void* batch_loop_kernel<T>(int pass, int mode, int cls, int shape) {
+  if (cls == kBatchBoth)  // (c2r and CN of both classes take a block per item)
+    return pass == BP_R2C ? reinterpret_cast<const void*>(kb_r2c_x_loop<T, 0, kBatchBoth, 0>)
+                          : reinterpret_cast<const void*>(kb_conv_y_loop<T, 0, kBatchBoth, 0>);
   if (cls == 0) return shape == 0 ? kernel_of<0, 0>(pass, mode) : kernel_of<0, 1>(pass, mode);
   return shape == 0 ? kernel_of<1, 0>(pass, mode) : kernel_of<1, 1>(pass, mode);
 }

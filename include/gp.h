@@ -267,10 +267,10 @@ gp_status gp_timing_burst(gp_ctx* ctx, int pass, int reps, double* ms_per_launch
 
 /* ------------------------------------------------------------ batched ensemble
  * Many independent quasi-2D instances (GP_2D_XY / GP_2D_XZ, any mix) of uneven sizes
- * and parameters, stepped together: each pass of a step is one persistent launch per
- * size class (lines <= 256 points, and 384/512) over a work list of (instance, tile)
- * items from every instance, sorted by decreasing instance size; one FP64 finalisation
- * block per instance.  Steps replay a captured HIP graph (8 steps) when nsteps >= 8.
+ * and parameters, stepped together: each pass of a step is one launch (per size class,
+ * lines <= 256 points and 384/512, where the launch plan sets a shape or block count) over
+ * a work list of (instance, tile) items from every instance, sorted by decreasing instance
+ * size; one FP64 finalisation block per instance.  Steps replay a captured HIP graph (8 steps) when nsteps >= 8.
  * All instances share one precision; every axis must be one of 32, 48, 64, 96, 128, 192,
  * 256, 384, 512 (else GP_E_SIZE).  The caller-owned workspace holds one single-grid
  * workspace per instance plus descriptors and work lists. */
@@ -293,9 +293,9 @@ gp_status gp_batch_step_real(gp_batch* batch, int nsteps);
 /* Observables of every instance's current psi (count records).  Synchronous. */
 gp_status gp_batch_energy(gp_batch* batch, gp_observables* out);
 /* Launch plan (autotuner interface).  items/blocks: arrays of 4 passes x 2 size classes
- * (r2c, conv, c2r, cn; class 0 = lines <= 256): work items and persistent blocks.
- * gp_batch_set_blocks sets the persistent block count of one (pass, class); 0 restores
- * the default (min(items, 1024)). */
+ * (r2c, conv, c2r, cn; class 0 = lines <= 256): work items and blocks.
+ * gp_batch_set_blocks sets the block count of one (pass, class), persistent blocks if
+ * fewer than the items; 0 restores the default (a block per item). */
 gp_status gp_batch_plan(gp_batch* batch, int* items, int* blocks);
 gp_status gp_batch_set_blocks(gp_batch* batch, int pass, int size_class, int blocks);
 /* Tile shape of one (pass, class), for the autotuner: 0 = the default tiles; 1 = x tiles

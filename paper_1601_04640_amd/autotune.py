@@ -2,7 +2,7 @@
 
 For every (pass, size class) of a `binding.Batch` it chooses the tile shape (the default
 tiles, or x and CN column tiles of 8 lines and line-FFT blocks of twice the points:
-`gp_batch_set_shape`) and the number of persistent blocks, timing a few graph-replayed
+`gp_batch_set_shape`) and the number of blocks, timing a few graph-replayed
 steps for each candidate and keeping the fastest, one coordinate at a time.  Results are
 cached in a JSON file keyed by the ensemble's size multiset, precision and device name, so
 a later run with the same ensemble reuses the plan.
@@ -45,7 +45,7 @@ def apply(batch, plan):
 
 
 def tune(batch, steps=16, imag=True, cache_path=None, verbose=False):
-    """Choose a tile shape and a persistent block count per (pass, size class); returns
+    """Choose a tile shape and a block count per (pass, size class); returns
     {"pass:class": {"shape": s, "blocks": g}}.  The instances' wave functions must be set
     (tuning steps evolve them)."""
     torch = batch.torch

@@ -570,8 +570,8 @@ BATCH_CLASSES = 2
 
 
 class Batch:
-    """Many independent quasi-2D instances stepped together (gp_batch_*): one persistent
-    launch per pass and size class.  params_list: dicts as for Solver (geom 2dxy/2dxz)."""
+    """Many independent quasi-2D instances stepped together (gp_batch_*): one launch per
+    pass.  params_list: dicts as for Solver (geom 2dxy/2dxz)."""
 
     def __init__(self, params_list, prec="fp32", device="cuda:0", stream=None):
         import torch

@@ -2,7 +2,9 @@
 // least 4 whose FFT line (the length, or Bluestein's M for a prime factor above 31) fits
 // one LDS buffer; longer 2D axes add the four-step passes of gp_long.hpp.  The line
 // length, the FFT's radix plan and the tile shapes are kernel arguments, so one set of
-// kernels serves every such grid.
+// kernels serves every such grid.  The main path of a step is in gp_rx.hpp (x passes),
+// gp_rfft.hpp (y and z lines) and gp_sweep.hpp (y and z sweeps); the kernels here run what
+// those do not take: long 2D axes, axes of a single radix, lines past their LDS.
 //
 // The step is the same split-step as the specialised passes ("Solution method": the
 // dipolar term by the convolution theorem, then the Crank-Nicolson sweeps; "Summary of
@@ -20,7 +22,6 @@
 //                   chunks' values in registers); the x sweep with the nonlinear
 //                   sub-step applied as it loads; optionally with the norm and
 //                   difference sums of the new state
-//                   (the y and z sweeps of lines up to 2048 points: gp_sweep.hpp)
 //   kg_cn_cols      the same sweep, one thread per strided line with the recurrence
 //                   values in a scratch grid: strided axes of more than 1024 points with
 //                   many lines, where consecutive threads read consecutive addresses

@@ -20,6 +20,13 @@ constexpr bool F32 = sizeof(T) == 4;
 constexpr int kSmall = r_max_radix<T>(false), kBig = r_max_radix<T>(true);
 constexpr int kWide = F32 ? 16 : 8;   // lines of a tile side by side: 128-byte runs
 
+// Whether the kernels of gp_generic.hpp have written-out butterflies for n points.
+bool seven_smooth(int n) {
+  for (int p : {2, 3, 5, 7})
+    while (n % p == 0) n /= p;
+  return n == 1;
+}
+
 #if GP_FAMILY == 0
 // every (lines per tile, largest radix) instantiated
 #if GP_RFFT_FP32
@@ -97,8 +104,15 @@ hipError_t RLaunch<T>::program(hipStream_t st, const RAxis& a, int kind, const v
   return hipGetLastError();
 }
 
+// Where one line takes more than half a CU's LDS, the kernels of gp_generic.hpp, whose lines
+// do not share it with the kernel values, are faster if they have the radices (y convolution
+// of 2048^2 FP64 50 us, 69 here; 4096^2 FP32 101 and 187; at 3600 FP32, with two blocks on a
+// CU, 27.7 and 24.8).
 template <>
-bool RLaunch<T>::contiguous_ok(const RAxis& a) { return fits(a, 1, lds_contiguous(a, 1, true), false); }
+bool RLaunch<T>::contiguous_ok(const RAxis& a) {
+  const size_t lds = lds_contiguous(a, 1, true);
+  return fits(a, 1, lds, false) && (lds <= 81920 || !seven_smooth(a.n));
+}
 
 template <>
 bool RLaunch<T>::strided_ok(const RAxis& a, int cols) {
@@ -194,6 +208,10 @@ template <typename F>
 RXCfg x_shape(const RAxis& a, int n1, int n2, F size) {
   RXCfg best;
   if (a.k < 2 || (double)a.n * (kWide + 1) * sizeof(cpx<T>) >= 2147483648.0) return best;
+  // longer lines leave a block few pairs; the kernels of gp_generic.hpp are faster if they
+  // have the radices (2500^2 FP32 36 + 28 + 88 us, 38 + 126 here; 2048^2 22 + 18 + 41 and
+  // 22 + 53)
+  if (a.n > 2048 && seven_smooth(a.n)) return best;
   const int pairs = (n1 + 1) / 2;
   for (int np = kWide / 2; np >= 1; np /= 2) {
     if (np > 1 && np / 2 >= pairs) continue;

@@ -256,12 +256,13 @@ RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
     return x_shape(a, n1, n2, [&](RXCfg& c) {
       const int tl = 2 * c.xt.np;
       const int sweep = (tl * ((a.n + rows - 1) / rows) + 63) / 64 * 64;
-      const int fft = r_spread<T>(a, c.xt.np, r_threads<T>(a, c.xt.np, false),
-                                  (long long)c.xt.nbj * n2);
+      const int base = r_threads<T>(a, c.xt.np, false);
+      int fft = r_spread<T>(a, c.xt.np, base, (long long)c.xt.nbj * n2);
+      if (fft > most && base <= most) fft = most;
       c.xt.S = rows;
       c.xt.P = sweep / tl;
       c.threads = sweep > fft ? sweep : fft;
-      if (c.threads > most) c.threads = 1 << 20;  // no such shape
+      if (c.threads > most || c.xt.P > kSweepMaxChunks) c.threads = 1 << 20;  // no such shape
       if (rows == 16 && c.xt.np == kWide / 2 && c.threads > 256) c.threads = 1 << 20;
       const size_t v = (size_t)a.m + (size_t)tl * c.xt.ls + 2 * (size_t)(sweep / 64) * tl +
                        (size_t)c.xt.P * (rows + kSweepGains);
@@ -273,12 +274,15 @@ RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
   // FP32 grids that fill the GPU sweep in chunks of 16 rows, 16 lines in a block of up to 256
   // threads or else 8, so that four or more blocks share a CU (a step of 400^3: 1524 us, 1541
   // with 16 lines in 512 threads; 390x90x90: 116.5 us, 130.1 with 8 rows); smaller ones in
-  // shorter chains of 8 (101x75x63: 20.0 us against 21.6 for this pass).
+  // shorter chains of 8 (101x75x63: 20.0 us against 21.6 for this pass), as long as the gain
+  // tables hold that many (to 2048 rows; a step of 2200x512 with 16 rows 61 us, 112 with every
+  // pass of gp_generic.hpp).
+  const RXCfg c8 = with(8, r_max_threads<T>());
   if (F32) {
-    const RXCfg c = with(16, 512);
-    if (c.blocks >= 1024) return c;
+    const RXCfg c16 = with(16, 512);
+    if (c16.blocks >= 1024 || c8.blocks == 0) return c16;
   }
-  return with(8, r_max_threads<T>());
+  return c8;
 }
 
 template <>

@@ -40,15 +40,17 @@ enum : int { SG_UP = 0, SG_UP_IN = 5, SG_DOWN = 6, SG_DOWN_IN = 11, SG_WAVE = 12
 //   [SG_UP_IN P + q]       over the chunks before q in its wave (1 for the first)
 //   [(SG_DOWN + s) P + q]  over q, q+1, ..     [SG_DOWN_IN P + q]  over those after q
 //   [SG_WAVE P + q]        over the whole wave
-// from the rounded factors, in FP64.  One thread per chunk, P <= 256 threads; P counts the
-// chunks of whole waves (those past the line have the identity map).
+// from the rounded factors, in FP64.  One thread per chunk, P <= kSweepMaxChunks; P counts
+// the chunks of whole waves (those past the line have the identity map).
+constexpr int kSweepMaxChunks = 256;
 struct SweepTables {
   const void* f[3];
   void* w[3];
 };
 template <typename T>
-__global__ void __launch_bounds__(256) k_sweep_gains(SweepTables t, int N, int S, int P, int QW) {
-  __shared__ double gr[256], gi[256];
+__global__ void __launch_bounds__(kSweepMaxChunks) k_sweep_gains(SweepTables t, int N, int S,
+                                                                 int P, int QW) {
+  __shared__ double gr[kSweepMaxChunks], gi[kSweepMaxChunks];
   const cpx<T>* __restrict__ f = reinterpret_cast<const cpx<T>*>(t.f[blockIdx.x]);
   cpx<T>* __restrict__ w = reinterpret_cast<cpx<T>*>(t.w[blockIdx.x]);
   const int q = threadIdx.x;

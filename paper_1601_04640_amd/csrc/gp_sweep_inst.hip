@@ -84,8 +84,9 @@ SweepCfg SweepLaunch<T>::cfg(int N, int n0, int n_outer, long long es) {
 template <>
 hipError_t SweepLaunch<T>::gains(const SweepCfg& c, hipStream_t st, const SweepTables& t, int N) {
   const int P = c.S ? c.chunks() : 0;
-  if (P < 1 || P > 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_sweep_gains<T>), dim3(3), dim3(256), 0, st, t, N, c.S, P, 64 / c.TC);
+  if (P < 1 || P > kSweepMaxChunks) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_sweep_gains<T>), dim3(3), dim3(kSweepMaxChunks), 0, st, t, N, c.S, P,
+                     64 / c.TC);
   return hipGetLastError();
 }
 

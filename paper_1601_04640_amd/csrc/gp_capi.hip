@@ -1323,7 +1323,9 @@ gp_status run_steps(gp_ctx* c, int nsteps, bool imag) {
   }
   if (!c->use_graphs || c->tmask != 0) {
     for (int done = 0; done < nsteps; ++done) GP_TRY(one_step(c, imag));
-    return GP_OK;
+    // A program may capture such a call into a graph of its own: on run-time lengths each
+    // replay is then whole steps, records included, with nothing left for a later call.
+    return c->L.generic ? settle(c) : GP_OK;
   }
   // a finalisation of the other time direction is completed first, so that every graph
   // starts from nothing outstanding or from one of its own direction
@@ -2015,6 +2017,10 @@ const char* gp_last_error(void) { return g_last_error; }
 
 gp_status gp_use_graphs(gp_ctx* c, int enable) {
   if (!c) return GP_E_ARG;
+  if (!enable) {
+    clear_stale_error();
+    GP_TRY(settle(c));
+  }
   c->use_graphs = enable != 0;
   return GP_OK;
 }

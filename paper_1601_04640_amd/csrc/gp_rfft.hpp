@@ -21,7 +21,6 @@
 namespace gpdbec {
 
 constexpr int kRMaxStages = 6;
-constexpr int kRMaxRadix = 16;
 // Largest block: FP32 kernels take at most 128 VGPRs.
 template <typename T>
 constexpr int r_max_threads() { return sizeof(T) == 4 ? 1024 : 512; }
@@ -237,12 +236,12 @@ struct Roots {
   }
 };
 
-template <typename T, int R, bool INV>
+template <typename T, int R>
 __device__ __forceinline__ void rdft(cpx<T>* x);
 
 // Odd prime P from the sums and differences of the pairs (s, P - s):
 // X_r, X_(P-r) = x_0 + sum_s a_s cos(2 pi r s/P) -+ i sum_s b_s sin(2 pi r s/P).
-template <typename T, int P, bool INV>
+template <typename T, int P>
 __device__ __forceinline__ void rdft_prime(cpx<T>* x) {
   constexpr int H = (P - 1) / 2;
   constexpr Roots<P> W{};
@@ -263,7 +262,7 @@ __device__ __forceinline__ void rdft_prime(cpx<T>* x) {
       C = C + scl(a[s - 1], c);
       S = S + scl(b[s - 1], n);
     }
-    const cpx<T> iS = INV ? cpx<T>{S.im, -S.re} : cpx<T>{-S.im, S.re};  // +-i S
+    const cpx<T> iS{-S.im, S.re};
     x[r] = C - iS;
     x[P - r] = C + iS;
   }
@@ -271,7 +270,7 @@ __device__ __forceinline__ void rdft_prime(cpx<T>* x) {
 
 // R = R1 R2: with n = R2 n1 + n2 and k = k1 + R1 k2,
 // X_k = sum_n2 W_R2^(n2 k2) W_R^(n2 k1) sum_n1 W_R1^(n1 k1) x_n.
-template <typename T, int R1, int R2, bool INV>
+template <typename T, int R1, int R2>
 __device__ __forceinline__ void rdft_split(cpx<T>* x) {
   constexpr int R = R1 * R2;
   constexpr Roots<R> W{};
@@ -280,33 +279,33 @@ __device__ __forceinline__ void rdft_split(cpx<T>* x) {
   for (int n2 = 0; n2 < R2; ++n2) {
 #pragma unroll
     for (int n1 = 0; n1 < R1; ++n1) y[n2][n1] = x[R2 * n1 + n2];
-    rdft<T, R1, INV>(y[n2]);
+    rdft<T, R1>(y[n2]);
 #pragma unroll
     for (int k1 = 1; k1 < R1; ++k1)
       if (n2 > 0)
-        y[n2][k1] = y[n2][k1] * cpx<T>{(T)W.c[n2 * k1], INV ? (T)W.s[n2 * k1] : (T)-W.s[n2 * k1]};
+        y[n2][k1] = y[n2][k1] * cpx<T>{(T)W.c[n2 * k1], (T)-W.s[n2 * k1]};
   }
 #pragma unroll
   for (int k1 = 0; k1 < R1; ++k1) {
     cpx<T> b[R2];
 #pragma unroll
     for (int n2 = 0; n2 < R2; ++n2) b[n2] = y[n2][k1];
-    rdft<T, R2, INV>(b);
+    rdft<T, R2>(b);
 #pragma unroll
     for (int k2 = 0; k2 < R2; ++k2) x[k1 + R1 * k2] = b[k2];
   }
 }
 
-template <typename T, int R, bool INV>
+template <typename T, int R>
 __device__ __forceinline__ void rdft(cpx<T>* x) {
-  if constexpr (R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 16) dft<T, R, INV>(x);
-  else if constexpr (R == 6) rdft_split<T, 3, 2, INV>(x);
-  else if constexpr (R == 9) rdft_split<T, 3, 3, INV>(x);
-  else if constexpr (R == 10) rdft_split<T, 5, 2, INV>(x);
-  else if constexpr (R == 12) rdft_split<T, 4, 3, INV>(x);
-  else if constexpr (R == 14) rdft_split<T, 7, 2, INV>(x);
-  else if constexpr (R == 15) rdft_split<T, 5, 3, INV>(x);
-  else rdft_prime<T, R, INV>(x);
+  if constexpr (R == 2 || R == 3 || R == 4 || R == 5 || R == 8 || R == 16) dft<T, R, false>(x);
+  else if constexpr (R == 6) rdft_split<T, 3, 2>(x);
+  else if constexpr (R == 9) rdft_split<T, 3, 3>(x);
+  else if constexpr (R == 10) rdft_split<T, 5, 2>(x);
+  else if constexpr (R == 12) rdft_split<T, 4, 3>(x);
+  else if constexpr (R == 14) rdft_split<T, 7, 2>(x);
+  else if constexpr (R == 15) rdft_split<T, 5, 3>(x);
+  else rdft_prime<T, R>(x);
 }
 
 // Butterflies of radix R that a thread holds at once: 10 values, 20 in the strided FP32 tiles
@@ -415,7 +414,7 @@ __device__ __forceinline__ void r_step(const RTile<NLC>& tile, const RProgram* _
           v[q][k] = cpx<T>{e < n ? x.re : (T)0, e < n ? x.im : (T)0};
         }
       }
-      rdft<T, R, false>(v[q]);
+      rdft<T, R>(v[q]);
       if (st.op != RO_NONE) {
 #pragma unroll
         for (int k = 0; k < R; ++k) {
@@ -436,7 +435,7 @@ __device__ __forceinline__ void r_step(const RTile<NLC>& tile, const RProgram* _
           }
           v[q][k] = conjg(x);
         }
-        rdft<T, R, false>(v[q]);
+        rdft<T, R>(v[q]);
       }
     }
   }

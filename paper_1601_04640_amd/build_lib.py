@@ -47,7 +47,7 @@ def _jobs(build_dir=BUILD, extra=()):
                            f"-DGP_SWEEP_FP32={int(real == 'float')}", "-c",
                            os.path.join(CSRC, "gp_sweep_inst.hip"), "-o", obj]))
     for real in ("float", "double"):
-        for fam in (0, 1):
+        for fam in (0, 1, 2, 3):
             obj = os.path.join(build_dir, f"rfft_{real}_{fam}.o")
             jobs.insert(0, (obj, [HIPCC, *FLAGS, *extra, f"-DGP_REAL={real}",
                                   f"-DGP_RFFT_FP32={int(real == 'float')}",

@@ -3,7 +3,8 @@
 // one stage to the next.
 //
 // A length whose prime factors are at most 13 runs Stockham stages of radices 2..16, as few
-// as possible (200 = 5 x 5 x 8, 400 = 4 x 10 x 10, 240 = 15 x 16).  The first stage reads its
+// as possible (200 = 5 x 5 x 8, 400 = 4 x 10 x 10, 240 = 15 x 16); the prime factors 17 to 31
+// are stages of their own, before the others (290 = 29 x 10).  The first stage reads its
 // operands from global memory and the last one leaves its results there, so an FFT of k
 // stages crosses LDS k - 1 times.  A convolution (transform, product, inverse transform)
 // runs the inverse with the radices in reverse order: the operands of its first stage are
@@ -21,6 +22,7 @@
 namespace gpdbec {
 
 constexpr int kRMaxStages = 6;
+constexpr int kRPrime = 31;  // largest prime factor with a stage of its own
 // Largest block: FP32 kernels take at most 128 VGPRs.
 template <typename T>
 constexpr int r_max_threads() { return sizeof(T) == 4 ? 1024 : 512; }
@@ -33,7 +35,8 @@ enum : int {
   RI_LDS = 0, RI_PLAIN, RI_CONJ, RI_BLUE, RI_BLUE_CONJ,
   // results: none of these (one butterfly), or an operation and the first butterfly of the
   // transform back (the radices reversed): the caller's product, Bluestein's filter, the end
-  // of one Bluestein transform with the product and the start of the next
+  // of one Bluestein transform with the product and the start of the next.  A radix past 16
+  // ends with the product, and the transform back begins with a step of its own.
   RO_NONE = 0, RO_PRODUCT, RO_FILTER, RO_BLUE_PRODUCT,
   // destination: LDS, or the caller's element
   RD_LDS = 0, RD_PLAIN, RD_CONJ, RD_BLUE, RD_BLUE_CONJ
@@ -97,8 +100,8 @@ inline int r_radices(int n, int maxr, int* out) {
 }
 
 // Stages of an n-point line: k radices for m points (n, or Bluestein's length), by kernels
-// that hold radices up to maxr.  k = 0: none, or a single radix (such short lines take the
-// other kernels).
+// that hold radices up to maxr.  k = 0: none, or a single radix up to 16 (such short lines
+// take the other kernels).
 struct RAxis {
   int n = 0, m = 0, k = 0, maxr = 0;
   int rad[kRMaxStages] = {};
@@ -136,6 +139,21 @@ inline RAxis r_axis(int n, long long points) {
   }
   a.m = n;
   if (a.k == 0) {
+    // Prime factors 17 to 31, then the rest.  (Bluestein's algorithm, two transforms and three
+    // rounded products for the one, has 1.1 to 2.9 times their error: Phi of 340 points along x
+    // FP64 8.6e-16 against 3.3e-16, of 380 along z 2.0e-15 against 6.8e-16.)
+    int rest = n, k = 0;
+    for (int q : {31, 29, 23, 19, 17})
+      for (; rest % q == 0 && k < kRMaxStages; rest /= q) a.rad[k++] = q;
+    int rad[kRMaxStages];
+    const int kr = rest > 1 ? r_radices(rest, r_max_radix<T>(true), rad) : 0;
+    if (k > 0 && k + kr <= kRMaxStages && (kr > 0 || rest == 1)) {
+      for (int i = 0; i < kr; ++i) a.rad[k + i] = rad[i];
+      a.k = k + kr;
+      a.maxr = kRPrime;
+    }
+  }
+  if (a.k == 0) {
     // Bluestein: among the lengths from 2n - 1 to a quarter more, the least values times
     // stages
     a.maxr = r_max_radix<T>(false);
@@ -150,7 +168,7 @@ inline RAxis r_axis(int n, long long points) {
       for (int i = 0; i < k; ++i) a.rad[i] = rad[i];
     }
   }
-  if (a.k < 2) a.k = 0;
+  if (a.k < 2 && a.maxr < kRPrime) a.k = 0;
   return a;
 }
 
@@ -163,13 +181,14 @@ inline void r_program(const RAxis& a, int kind, RProgram* p) {
   p->steps = 0;
   p->tw = p->chirp = p->filt = nullptr;
   // transforms run one after the other, every second one with the radices reversed; the last
-  // stage of one and the first of the next are one step
+  // stage of one and the first of the next are one step (two of a radix past 16)
+  const bool fused = rad[k - 1] <= 16;
   const int nt = (blue ? 2 : 1) * (kind == RL_CONV ? 2 : 1);
   for (int t = 0; t < nt; ++t) {
     int L = 1;
     for (int i = 0; i < k; ++i) {
       const int r = t % 2 ? rad[k - 1 - i] : rad[i];
-      if (t == 0 || i > 0) {
+      if (t == 0 || i > 0 || !fused) {
         RStep& s = p->st[p->steps++];
         s.rad = (uint8_t)r;
         s.nb = p->m / r;
@@ -330,13 +349,23 @@ inline int r_threads(const RAxis& a, int nl, bool strided) {
 }
 
 // Threads of a pass of few blocks: doubled while the GPU has room (two waves per SIMD, one
-// on a CU's every SIMD for each of 256 blocks) and a stage has a butterfly for each, so that
-// a wave issues fewer instructions one after the other.
+// on a CU's every SIMD for each of 256 blocks) and a stage has a butterfly for each (a prime
+// past 16: a few waves for each wave of butterflies), so that a wave issues fewer instructions
+// one after the other.
+// Waves of one butterfly's threads that pairs of results are dealt to (62x58x68 FP64 96 us a
+// step with one; 76 with four, of which grids that fill the GPU keep fewer).
+constexpr int kRShares = 4;
 template <typename T>
 inline int r_spread(const RAxis& a, int nl, int threads, long long blocks) {
   int wide = 0;
-  for (int s = 0; s < a.k; ++s) wide = nl * (a.m / a.rad[s]) > wide ? nl * (a.m / a.rad[s]) : wide;
-  while (threads < wide && 2 * threads <= r_max_threads<T>() && 2 * threads * blocks <= 256 * 1024)
+  for (int s = 0; s < a.k; ++s) {
+    int w = nl * (a.m / a.rad[s]);
+    if (a.rad[s] > 16) w = (w + 63) / 64 * 64 * kRShares;
+    wide = w > wide ? w : wide;
+  }
+  // (the FP64 kernels with primes past 16 have half the waves)
+  const long long room = sizeof(T) == 8 && a.maxr == kRPrime ? 128 * 1024 : 256 * 1024;
+  while (threads < wide && 2 * threads <= r_max_threads<T>() && 2 * threads * blocks <= room)
     threads *= 2;
   return threads;
 }
@@ -474,6 +503,142 @@ __device__ __forceinline__ void r_step(const RTile<NLC>& tile, const RProgram* _
   }
 }
 
+// cos and sin of 2 pi s / P, 0 < s < P / 2, rounded once.
+template <typename T, int P>
+struct HalfRoots {
+  T c[(P - 1) / 2], s[(P - 1) / 2];
+  constexpr HalfRoots() : c(), s() {
+    constexpr Roots<P> W{};
+    for (int k = 0; k < (P - 1) / 2; ++k) {
+      c[k] = (T)W.c[k + 1];
+      s[k] = (T)W.s[k + 1];
+    }
+  }
+};
+template <typename T, int P>
+static __constant__ HalfRoots<T, P> r_half_roots = HalfRoots<T, P>{};
+
+// The same with a prime radix past 16.  A thread holds the sums and differences of
+// rdft_prime of one butterfly, and each pair of results goes where it belongs as soon as it is
+// summed (31 FP64 values and their results together would not fit the registers).  Threads
+// past the butterflies take whole waves' shares of the pairs.  The roots come from constant
+// memory by scalar loads, once a step (as literals they spilled 358 SGPRs in FP64, and loaded
+// pair by pair in a loop they stand in the way of the multiply-adds: 290^3 FP64 1838 us a step,
+// 1642 so), rounded once: the twiddle table's, whose arguments are rounded too, leave the
+// residue of a constant line behind (Phi of 38 points along z FP64 7.9e-16 against 5.6e-16).
+// RO_PRODUCT: the product goes to LDS, conjugated, where the transform back begins.
+//
+// A butterfly of 31 values is 900 multiply-adds in one thread: what bounds it on large grids,
+// and on small ones the few lanes that have one.  A step of 290^3 takes 677 us FP32 and 1642 FP64
+// (with Bluestein's algorithm 1544 and 2491), 340x310 37 and 42 (53 and 56), 62x58x68 54 and
+// 76 (73 and 68).
+template <typename T, int P, bool ALIAS, int NLC, typename Load, typename Product,
+          typename Store, typename First>
+__device__ __forceinline__ void r_step_prime(const RTile<NLC>& tile, const RStep& st,
+                                             const cpx<T>* tw, cpx<T>* buf, Load load,
+                                             Product product, Store store, First first) {
+  constexpr int H = (P - 1) / 2;
+  const int nb = st.nb, L = st.L, tot = tile.lines() * nb;
+  // the roots' address is opaque to the compiler, which would make them literals again
+  typedef const __attribute__((address_space(4))) T* Roots4;
+  uintptr_t wa = (uintptr_t)&r_half_roots<T, P>;
+  asm("" : "+s"(wa));
+  T wc[H], ws[H];
+#pragma unroll
+  for (int s = 0; s < H; ++s) {
+    wc[s] = ((Roots4)wa)[s];
+    ws[s] = ((Roots4)wa)[H + s];
+  }
+  // shares of the pairs: whole waves (a line read and left in global memory has one)
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int tw_ = (tot + 63) >> 6, nw = (int)blockDim.x >> 6;
+  const int shares = st.in != RI_LDS && st.out != RD_LDS ? 1 : nw / tw_;
+  const int share = wave / tw_;
+  const int u = (int)threadIdx.x - share * tw_ * 64;
+  const bool on = share < shares && u < tot;
+  int l = 0, t = 0, j = 0;
+  cpx<T> x0{0, 0}, a[H], b[H];
+  if (on) {
+    tile.locate(u, st.fnb(), nb, &l, &t);
+    j = t - (int)fdiv((uint32_t)t, st.fl()) * L;
+    if (st.in == RI_LDS) {
+      x0 = buf[tile.at(l, t)];
+#pragma unroll
+      for (int s = 1; s <= H; ++s) {
+        a[s - 1] = buf[tile.at(l, t + s * nb)];
+        b[s - 1] = buf[tile.at(l, t + (P - s) * nb)];
+      }
+#pragma unroll
+      for (int s = 1; s <= H; ++s) {
+        a[s - 1] = a[s - 1] * tw[s * j * st.ts];
+        b[s - 1] = b[s - 1] * tw[(P - s) * j * st.ts];
+      }
+    } else {
+      x0 = load(l, t);
+#pragma unroll
+      for (int s = 1; s <= H; ++s) {
+        a[s - 1] = load(l, t + s * nb);
+        b[s - 1] = load(l, t + (P - s) * nb);
+      }
+      if (st.in == RI_CONJ) {
+        x0 = conjg(x0);
+#pragma unroll
+        for (int s = 0; s < H; ++s) {
+          a[s] = conjg(a[s]);
+          b[s] = conjg(b[s]);
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < H; ++s) {
+      const cpx<T> d = a[s] - b[s];
+      a[s] = a[s] + b[s];
+      b[s] = d;
+    }
+  }
+  if (st.in != RI_LDS) first();
+  // every operand is read, and what first() keeps for the product of a line of one stage is there
+  if (ALIAS || (st.out == RD_LDS && (st.in == RI_LDS || st.op != RO_NONE))) __syncthreads();
+  if (on) {
+    const bool turn = st.op != RO_NONE;
+    const int o = turn ? t : (t - j) * P + j, d = turn ? nb : L;
+    auto put = [&](int k, cpx<T> v) {
+      if (st.out == RD_LDS) {
+        if (turn) v = conjg(product(l, t + k * nb, v));
+        buf[tile.at(l, o + k * d)] = v;
+      } else {
+        if (st.out == RD_CONJ) v.im = -v.im;
+        store(l, t + k * nb, v);  // the last stage: L = nb, j = t
+      }
+    };
+    if (share == 0) {
+      cpx<T> sum = x0;
+#pragma unroll
+      for (int s = 0; s < H; ++s) sum = sum + a[s];
+      put(0, sum);
+    }
+    int next = share;  // the pairs share, share + shares, ...
+#pragma unroll
+    for (int r = 1; r <= H; ++r) {
+      if (next-- == 0) {
+        next = shares - 1;
+        cpx<T> C = x0, S = {0, 0};
+#pragma unroll
+        for (int s = 1; s <= H; ++s) {
+          const int k = (r * s) % P;
+          const T c = wc[(k <= H ? k : P - k) - 1], n = ws[(k <= H ? k : P - k) - 1];
+          C = C + scl(a[s - 1], c);
+          S = k <= H ? S + scl(b[s - 1], n) : S - scl(b[s - 1], n);
+        }
+        const cpx<T> iS{-S.im, S.re};
+        put(r, C - iS);
+        put(P - r, C + iS);
+      }
+    }
+  }
+  if (st.out == RD_LDS) __syncthreads();
+}
+
 // The program of a tile's lines.  tw: its twiddles in LDS (the first step reads none, so
 // first() may write them); buf: LDS of the tile, free.
 template <typename T, int MAXR, bool ALIAS, int NLC, typename Load, typename Product,
@@ -489,10 +654,17 @@ __device__ __forceinline__ void r_run(const RTile<NLC>& tile, const RProgram* __
     switch (st.rad) {
 #define GP_R(R)                                                      \
   case R:                                                            \
-    if constexpr (R <= MAXR) r_step<T, R, ALIAS>(tile, p, st, tw, buf, load, product, store, first); \
+    if constexpr (R <= MAXR && R <= r_max_radix<T>(true))            \
+      r_step<T, R, ALIAS>(tile, p, st, tw, buf, load, product, store, first); \
     break;
       GP_R(2) GP_R(3) GP_R(4) GP_R(5) GP_R(6) GP_R(7) GP_R(8) GP_R(9) GP_R(10) GP_R(11) GP_R(12)
       GP_R(13) GP_R(14) GP_R(15) GP_R(16)
+#undef GP_R
+#define GP_R(R)                                                      \
+  case R:                                                            \
+    if constexpr (R <= MAXR) r_step_prime<T, R, ALIAS>(tile, st, tw, buf, load, product, store, first); \
+    break;
+      GP_R(17) GP_R(19) GP_R(23) GP_R(29) GP_R(31)
 #undef GP_R
       default:
         break;

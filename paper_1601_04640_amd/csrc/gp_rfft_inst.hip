@@ -1,5 +1,6 @@
 // Instantiations of the run-time-length FFT passes for one precision (GP_REAL) and family:
 //   GP_FAMILY 0: line passes and programs    1: x passes
+//   2 and 3: the kernels of both that hold the prime radices past 16 (compiled apart)
 #include <mutex>
 
 #include "gp_rfft_launch.hpp"
@@ -11,6 +12,37 @@
 namespace gpdbec {
 using T = GP_REAL;
 
+// Families 2 and 3 define these kernels, 0 and 1 launch them.
+#if GP_FAMILY >= 2
+#define GP_PRIME_KERNEL template __global__ void
+#else
+#define GP_PRIME_KERNEL extern template __global__ void
+#endif
+#if GP_FAMILY % 2 == 0
+#define X(NLC)                                                                                \
+  GP_PRIME_KERNEL k_rlines<T, NLC, kRPrime>(cpx<T>*, RLines, const RProgram*, const T*,       \
+                                            const double*, FoldedFin);
+X(0) X(8) X(4)
+#if GP_RFFT_FP32
+X(16)
+#else
+X(2)
+#endif
+#undef X
+#else
+GP_PRIME_KERNEL k_rr2c<T, kRPrime>(const cpx<T>*, cpx<T>*, RXTile, const RProgram*, double*,
+                                   FoldedFin);
+#define X(MODE, S)                                                                            \
+  GP_PRIME_KERNEL k_rc2r<T, kRPrime, MODE, S>(const cpx<T>*, RXTile, const RProgram*, RXArgs<T>);
+X(MODE_IMAG, 8) X(MODE_REAL, 8) X(MODE_OBSERVE, 8)
+#if GP_RFFT_FP32
+X(MODE_IMAG, 16) X(MODE_REAL, 16)
+#endif
+#undef X
+#endif
+#undef GP_PRIME_KERNEL
+
+#if GP_FAMILY < 2
 #if GP_FAMILY == 0
 hipError_t rx_prepare(T);  // the x passes' LDS limits (family 1)
 #endif
@@ -30,10 +62,14 @@ bool seven_smooth(int n) {
 #if GP_FAMILY == 0
 // every (lines per tile, largest radix) instantiated
 #if GP_RFFT_FP32
-#define GP_FOR_RLINES(X) X(0, kSmall) X(16, kSmall) X(8, kSmall) X(4, kSmall)
+#define GP_FOR_RLINES(X)                                  \
+  X(0, kSmall) X(16, kSmall) X(8, kSmall) X(4, kSmall)    \
+  X(0, kRPrime) X(16, kRPrime) X(8, kRPrime) X(4, kRPrime)
 #else
-#define GP_FOR_RLINES(X) \
-  X(0, kSmall) X(8, kSmall) X(4, kSmall) X(2, kSmall) X(0, kBig) X(8, kBig) X(4, kBig) X(2, kBig)
+#define GP_FOR_RLINES(X)                                  \
+  X(0, kSmall) X(8, kSmall) X(4, kSmall) X(2, kSmall)     \
+  X(0, kBig) X(8, kBig) X(4, kBig) X(2, kBig)             \
+  X(0, kRPrime) X(8, kRPrime) X(4, kRPrime) X(2, kRPrime)
 #endif
 constexpr int kNarrow = F32 ? 4 : 2;
 
@@ -94,7 +130,7 @@ hipError_t RLaunch<T>::prepare() {
 template <>
 hipError_t RLaunch<T>::program(hipStream_t st, const RAxis& a, int kind, const void* tw,
                                const void* chirp, const void* filt, RProgram* dst) {
-  if (a.k < 2 || a.k > kRMaxStages) return hipErrorInvalidValue;
+  if (a.k < 1 || a.k > kRMaxStages) return hipErrorInvalidValue;
   RProgram p{};
   r_program(a, kind, &p);
   p.tw = tw;
@@ -130,6 +166,9 @@ hipError_t launch(hipStream_t st, int blocks, int threads, size_t lds, cpx<T>* d
   if (lds < kFoldedLds) lds = kFoldedLds;
   if (maxr == kSmall)
     hipLaunchKernelGGL((k_rlines<T, NLC, kSmall>), dim3(blocks), dim3(threads), lds, st, data, g,
+                       p, ktab, scale, fin);
+  else if (maxr == kRPrime)
+    hipLaunchKernelGGL((k_rlines<T, NLC, kRPrime>), dim3(blocks), dim3(threads), lds, st, data, g,
                        p, ktab, scale, fin);
   else
     hipLaunchKernelGGL((k_rlines<T, NLC, kBig>), dim3(blocks), dim3(threads), lds, st, data, g, p,
@@ -184,10 +223,12 @@ hipError_t rx_prepare(T) {
       reinterpret_cast<const void*>(&k_rc2r<T, M, MODE_IMAG, 8>),  \
       reinterpret_cast<const void*>(&k_rc2r<T, M, MODE_REAL, 8>),  \
       reinterpret_cast<const void*>(&k_rc2r<T, M, MODE_OBSERVE, 8>)
-      X(kSmall),
+      X(kSmall), X(kRPrime),
 #if GP_RFFT_FP32
       reinterpret_cast<const void*>(&k_rc2r<T, kSmall, MODE_IMAG, 16>),
       reinterpret_cast<const void*>(&k_rc2r<T, kSmall, MODE_REAL, 16>),
+      reinterpret_cast<const void*>(&k_rc2r<T, kRPrime, MODE_IMAG, 16>),
+      reinterpret_cast<const void*>(&k_rc2r<T, kRPrime, MODE_REAL, 16>),
 #else
       X(kBig),
 #endif
@@ -207,7 +248,7 @@ namespace {
 template <typename F>
 RXCfg x_shape(const RAxis& a, int n1, int n2, F size) {
   RXCfg best;
-  if (a.k < 2 || (double)a.n * (kWide + 1) * sizeof(cpx<T>) >= 2147483648.0) return best;
+  if (a.k < 1 || (double)a.n * (kWide + 1) * sizeof(cpx<T>) >= 2147483648.0) return best;
   // longer lines leave a block few pairs; the kernels of gp_generic.hpp are faster if they
   // have the radices (2500^2 FP32 36 + 28 + 88 us, 38 + 126 here; 2048^2 22 + 18 + 41 and
   // 22 + 53)
@@ -292,6 +333,9 @@ hipError_t RLaunch<T>::r2c(hipStream_t st, const RXCfg& c, const RAxis& a, const
   if (a.maxr == kSmall)
     hipLaunchKernelGGL((k_rr2c<T, kSmall>), dim3(c.blocks + fin.lead), dim3(c.threads), c.lds, st,
                        psi, spec, c.xt, p, part, fin);
+  else if (a.maxr == kRPrime)
+    hipLaunchKernelGGL((k_rr2c<T, kRPrime>), dim3(c.blocks + fin.lead), dim3(c.threads), c.lds,
+                       st, psi, spec, c.xt, p, part, fin);
   else
     hipLaunchKernelGGL((k_rr2c<T, kBig>), dim3(c.blocks + fin.lead), dim3(c.threads), c.lds, st,
                        psi, spec, c.xt, p, part, fin);
@@ -307,7 +351,9 @@ hipError_t RLaunch<T>::c2r(hipStream_t st, const RXCfg& c, const RAxis& a, int m
                      c.xt, p, g)
 #define GP_C2R_MODE(MD)                                            \
   case MD:                                                         \
-    if (a.maxr != kSmall) GP_C2R(kBig, MD, 8);                     \
+    if (a.maxr == kRPrime && F32 && c.xt.S == 16) GP_C2R(kRPrime, MD, (F32 ? 16 : 8)); \
+    else if (a.maxr == kRPrime) GP_C2R(kRPrime, MD, 8);            \
+    else if (a.maxr != kSmall) GP_C2R(kBig, MD, 8);                \
     else if (F32 && c.xt.S == 16) GP_C2R(kSmall, MD, (F32 ? 16 : 8)); \
     else GP_C2R(kSmall, MD, 8);                                    \
     break;
@@ -315,7 +361,8 @@ hipError_t RLaunch<T>::c2r(hipStream_t st, const RXCfg& c, const RAxis& a, int m
     GP_C2R_MODE(MODE_IMAG)
     GP_C2R_MODE(MODE_REAL)
     case MODE_OBSERVE:
-      if (a.maxr != kSmall) GP_C2R(kBig, MODE_OBSERVE, 8);
+      if (a.maxr == kRPrime) GP_C2R(kRPrime, MODE_OBSERVE, 8);
+      else if (a.maxr != kSmall) GP_C2R(kBig, MODE_OBSERVE, 8);
       else GP_C2R(kSmall, MODE_OBSERVE, 8);
       break;
     default:
@@ -325,6 +372,7 @@ hipError_t RLaunch<T>::c2r(hipStream_t st, const RXCfg& c, const RAxis& a, int m
 #undef GP_C2R
   return hipGetLastError();
 }
-#endif
+#endif  // x passes
+#endif  // GP_FAMILY < 2
 
 }  // namespace gpdbec

@@ -156,9 +156,12 @@ struct RXArgs {
 // FFT: Phi of line j in the real parts, of line j + 1 in the imaginary ones.
 // MODE_IMAG / MODE_REAL: psi <- sweep of scale psi exp(-eps dt (V + g_c n + g_dd Phi)), and
 // part[7b..] = sums n, V n, n^2, Phi n, x^2 n, y^2 n, z^2 n of scale psi.  MODE_OBSERVE: the
-// sums where part is given, Phi where phi is.  S: rows per chunk of the sweep.
+// sums where part is given, Phi where phi is.  S: rows per chunk of the sweep.  Four waves per
+// SIMD are asked for (1 to 12 VGPRs spilled: FP64, and FP32 with 16 rows in real time), two of
+// the FP64 kernels with primes past 16 (202-220 VGPRs).
 template <typename T, int MAXR, int MODE, int S>
-__global__ void __launch_bounds__(r_max_threads<T>(), 4) k_rc2r(const cpx<T>* __restrict__ spec, RXTile xt,
+__global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 16 ? 2 : 4))
+    k_rc2r(const cpx<T>* __restrict__ spec, RXTile xt,
                                                     const RProgram* __restrict__ p,
                                                     RXArgs<T> g) {
   constexpr bool STEP = MODE == MODE_IMAG || MODE == MODE_REAL;

@@ -35,6 +35,11 @@ static void lengths(const char* prec) {
     for (const auto& o : others) {
       const int n1 = o[0], n2 = o[1];
       const RAxis a = r_axis<T>(n, (long long)n * n1 * n2);
+      // prime factors to 31 have stages of their own; Bluestein's algorithm is for the others
+      int rest = n;
+      for (int q = 2; q <= 31; ++q)
+        while (rest % q == 0) rest /= q;
+      check(a.k == 0 || a.blue() == (rest > 1), "direct", prec, n, n1, n2, a.m);
       const RXCfg r = RLaunch<T>::x_r2c(a, n1, n2), c = RLaunch<T>::x_c2r(a, n1, n2);
       for (const RXCfg* x : {&r, &c}) {
         if (x->blocks == 0) continue;

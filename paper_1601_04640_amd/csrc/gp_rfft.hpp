@@ -525,7 +525,7 @@ static __constant__ HalfRoots<T, P> r_half_roots = HalfRoots<T, P>{};
 // memory by scalar loads, once a step (as literals they spilled 358 SGPRs in FP64, and loaded
 // pair by pair in a loop they stand in the way of the multiply-adds: 290^3 FP64 1838 us a step,
 // 1642 so), rounded once: the twiddle table's, whose arguments are rounded too, leave the
-// residue of a constant line behind (Phi of 38 points along z FP64 7.9e-16 against 5.6e-16).
+// residue of a constant line behind (Phi of 38 points along z FP64 7.9e-16 against 5.4e-16).
 // RO_PRODUCT: the product goes to LDS, conjugated, where the transform back begins.
 //
 // A butterfly of 31 values is 900 multiply-adds in one thread: what bounds it on large grids,

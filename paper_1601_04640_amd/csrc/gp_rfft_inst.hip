@@ -1,6 +1,7 @@
 // Instantiations of the run-time-length FFT passes for one precision (GP_REAL) and family:
 //   GP_FAMILY 0: line passes and programs    1: x passes
 //   2 and 3: the kernels of both that hold the prime radices past 16 (compiled apart)
+#include <algorithm>
 #include <mutex>
 
 #include "gp_rfft_launch.hpp"
@@ -305,11 +306,10 @@ RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
       c.threads = sweep > fft ? sweep : fft;
       if (c.threads > most || c.xt.P > kSweepMaxChunks) c.threads = 1 << 20;  // no such shape
       if (rows == 16 && c.xt.np == kWide / 2 && c.threads > 256) c.threads = 1 << 20;
-      const size_t v = (size_t)a.m + (size_t)tl * c.xt.ls + 2 * (size_t)(sweep / 64) * tl +
-                       (size_t)c.xt.P * (rows + kSweepGains);
-      c.lds = sizeof(cpx<T>) * v;
-      const size_t least = sizeof(cpx<T>) * (size_t)a.m + 1024;  // the reduction
-      if (c.lds < least) c.lds = least;
+      // the twiddles, then the factors; the lines; the waves' carries and gains; the sums
+      const size_t nw = sweep / 64, pre = std::max((size_t)a.m, (size_t)c.xt.P * rows);
+      c.lds = sizeof(cpx<T>) * (pre + (size_t)tl * c.xt.ls + 2 * nw * tl + nw) +
+              7 * 16 * sizeof(double);
     });
   };
   // FP32 grids that fill the GPU sweep in chunks of 16 rows, 16 lines in a block of up to 256
@@ -317,11 +317,12 @@ RXCfg RLaunch<T>::x_c2r(const RAxis& a, int n1, int n2) {
   // with 16 lines in 512 threads; 390x90x90: 116.5 us, 130.1 with 8 rows); smaller ones in
   // shorter chains of 8 (101x75x63: 20.0 us against 21.6 for this pass), as long as the gain
   // tables hold that many (to 2048 rows; a step of 2200x512 with 16 rows 61 us, 112 with every
-  // pass of gp_generic.hpp).
+  // pass of gp_generic.hpp).  One-pair tiles keep 8 rows: 2048^2 118 us against 125 with 16,
+  // 2000x2048 112 and 118 (of 3D grids 2000x60x50 174 against 168, 2048x100x100 522 against 552).
   const RXCfg c8 = with(8, r_max_threads<T>());
   if (F32) {
     const RXCfg c16 = with(16, 512);
-    if (c16.blocks >= 1024 || c8.blocks == 0) return c16;
+    if ((c16.blocks >= 1024 && c16.xt.np > 1) || c8.blocks == 0) return c16;
   }
   return c8;
 }

@@ -22,19 +22,21 @@ struct RXTile {
 };
 
 
-// Sums of NV values over a block of whole waves (at most 16), in a fixed order: thread v
-// stores total v.  red: NV x 16 doubles.
+// Sums of NV values over a block of whole waves (at most 16), in a fixed order: each wave's to
+// red (NV x 16 doubles), and, a barrier later, total v stored by thread v.
 template <int NV>
-__device__ __forceinline__ void rx_block_store(double (&v)[NV], double* red,
-                                               double* __restrict__ out) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+__device__ __forceinline__ void rx_block_reduce(double (&v)[NV], double* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < NV; ++k) v[k] = wave_sum_to_last(v[k]);
   if (lane == 63) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) red[k * 16 + wave] = v[k];
   }
-  __syncthreads();
+}
+template <int NV>
+__device__ __forceinline__ void rx_block_total(const double* red, double* __restrict__ out) {
+  const int nw = blockDim.x >> 6;
   if ((int)threadIdx.x < NV) {
     double acc = red[threadIdx.x * 16];
     for (int w = 1; w < nw; ++w) acc += red[threadIdx.x * 16 + w];
@@ -135,7 +137,9 @@ __global__ void __launch_bounds__(r_max_threads<T>()) k_rr2c(const cpx<T>* __res
     }
   }
   __syncthreads();  // the line buffer is free: it holds the reduction
-  rx_block_store<2>(s, reinterpret_cast<double*>(buf), part + 2 * (long long)bid);
+  rx_block_reduce<2>(s, reinterpret_cast<double*>(buf));
+  __syncthreads();
+  rx_block_total<2>(reinterpret_cast<double*>(buf), part + 2 * (long long)bid);
 }
 
 // What the complex-to-real pass works on: psi, V, the scale of psi, the x factors and their
@@ -156,9 +160,18 @@ struct RXArgs {
 // FFT: Phi of line j in the real parts, of line j + 1 in the imaginary ones.
 // MODE_IMAG / MODE_REAL: psi <- sweep of scale psi exp(-eps dt (V + g_c n + g_dd Phi)), and
 // part[7b..] = sums n, V n, n^2, Phi n, x^2 n, y^2 n, z^2 n of scale psi.  MODE_OBSERVE: the
-// sums where part is given, Phi where phi is.  S: rows per chunk of the sweep.  Four waves per
-// SIMD are asked for (1 to 12 VGPRs spilled: FP64, and FP32 with 16 rows in real time), two of
-// the FP64 kernels with primes past 16 (202-220 VGPRs).
+// sums where part is given, Phi where phi is.  S: rows per chunk of the sweep.
+//
+// LDS bounds the blocks on a CU and the pairs in a block, so it holds what is live: both lines
+// of every pair, the twiddles and then, in their place, the sweep's factors.  The scans' gains,
+// of which a thread needs its own chunk's once, come from L2 into registers.  With factors and
+// gains beside the twiddles 640 points FP64 were 66 KB for one pair (two fit 58 KB now), 1200 110 KB
+// (65), 2000 points FP32 132 KB for two pairs (54 for one); a step of 640^3 FP64 took 16.1 ms in
+// imaginary and 17.0 in real time (13.6 and 14.2 now), 1200x2400 237 and 250 us (210 and 218),
+// 700x3600 208 and 220 (196 and 206), 2000x1500 FP32 95 and 101 (90 and 94).
+//
+// Four waves per SIMD are asked for (3 or 4 VGPRs spilled in FP64 real time, 1 in FP32 with 16
+// rows and primes past 16), two of the FP64 kernels with primes past 16 (202-208 VGPRs).
 template <typename T, int MAXR, int MODE, int S>
 __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 16 ? 2 : 4))
     k_rc2r(const cpx<T>* __restrict__ spec, RXTile xt,
@@ -171,13 +184,15 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
   constexpr int U = sizeof(T) == 4 ? 4 : 2;
   extern __shared__ __align__(16) char rx_raw[];
   const int N = xt.n0, n1 = xt.n1, m = p->m, nt = blockDim.x, tid = threadIdx.x;
+  const int TL = 2 * xt.np, P = xt.P, nw = P * TL >> 6;  // waves that sweep
   cpx<T>* tw = reinterpret_cast<cpx<T>*>(rx_raw);
-  cpx<T>* buf = tw + m;                       // line 2q of the tile (Z of the pair before)
+  cpx<T>* buf = tw + max(m, P * S);           // line 2q of the tile (Z of the pair before)
   cpx<T>* odd = buf + xt.np * xt.ls;          // line 2q + 1
   cpx<T>* wD = odd + xt.np * xt.ls;           // the sweep: the waves' carries,
-  const int TL = 2 * xt.np, P = xt.P, nw = P * TL >> 6;  // waves that sweep
-  GT* fs = reinterpret_cast<GT*>(wD + 2 * nw * TL);  // factors of P chunks and their gains
-  GT* gs = fs + P * S;
+  GT* fs = reinterpret_cast<GT*>(tw);  // after the FFT: the factors of P chunks
+  GT* gw = reinterpret_cast<GT*>(wD + 2 * nw * TL);  // gains of the waves
+  double* red = reinterpret_cast<double*>(wD + 2 * nw * TL + nw);
+  const int lg = 31 - __clz(TL), QW = 64 >> lg;      // chunks of a line in a wave
   const int b = xcd_tile(blockIdx.x, gridDim.x);
   const int k = b / xt.nbj, j0 = (b - k * xt.nbj) * TL;
   const int lines = min(TL, n1 - j0), npairs = (lines + 1) / 2;
@@ -187,12 +202,10 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
   auto f_of = [&](int t) { return CnArith<T, IMAG_A>{}.gain(t < N ? g.f[t] : cpx<T>{0, 0}); };
   auto g_of = [&](int t) { return scan_weight<GT>(g.gains + t); };
   Prefetch<cpx<T>, 1> ptw;
-  Prefetch<GT, 1> pf;
-  Prefetch<GT, 2> pg;
+  GT wave_gain{};
   ptw.load(m, tw_of);
   if constexpr (STEP) {
-    pf.load(P * S, f_of);
-    pg.load(P * kSweepGains, g_of);
+    wave_gain = g_of(SG_WAVE * P + min(tid, nw - 1) * QW);
   }
   // the spectrum of the pairs
   {
@@ -242,8 +255,7 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
       [&] {
         ptw.store(m, tw, tw_of);
         if constexpr (STEP) {
-          pf.store(P * S, fs, f_of);
-          pg.store(P * kSweepGains, gs, g_of);
+          if (tid < nw) gw[tid] = wave_gain;
         }
       });
   __syncthreads();
@@ -317,14 +329,26 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
     }
     s[6] = z * z * s[0];
   }
+  // the gains of the sweep's scans: each of the chunk's own once, straight from L2
+  Prefetch<GT, 4> pf;
+  GT up[5], up_in{};
+  const int q = STEP ? min(tid >> lg, P - 1) : 0;
   if constexpr (STEP) {
+    pf.load(P * S, f_of);
+#pragma unroll
+    for (int st = 0; st < 5; ++st) up[st] = g_of((SG_UP + st) * P + q);
+    up_in = g_of(SG_UP_IN * P + q);
+  }
+  if (STEP || g.part != nullptr) rx_block_reduce<7>(s, red);
+  if constexpr (STEP) {
+    pf.store(P * S, fs, f_of);  // the FFT is done with the twiddles
     __syncthreads();
     // the sweep: thread (line l, chunk q), as in gp_sweep.hpp with the rows in LDS
     const cpx<T> zero{0, 0};
-    const int lg = 31 - __clz(TL), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // waves past the sweep's repeat its last chunks; neither they nor lines past the tile
     // store anything
-    const int l = tid & (TL - 1), q = min(tid >> lg, P - 1), lo = q * S;
+    const int l = tid & (TL - 1), lo = q * S;
     const bool act = l < lines && wave < nw;
     cpx<T>* ln = (l & 1 ? odd : buf) + (l < lines ? l >> 1 : 0) * xt.ls;
     auto at = [&](int i) { return i + (i >> 3); };
@@ -352,18 +376,25 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
         D = r[e] + mulg(gg, D);
       }
     }
-    int st = 0;
-    for (int off = TL; off < 64; off <<= 1, ++st) {
+#pragma unroll
+    for (int st = 0; st < 5; ++st) {
+      const int off = TL << st;
+      if (off >= 64) break;
       const cpx<T> Dn = lane_at(D, (lane - off) * 4);
-      D = csel(lane >= off, D + mulg(gs[(SG_UP + st) * P + q], Dn), D);
+      D = csel(lane >= off, D + mulg(up[st], Dn), D);
     }
+    // those down: all at once, or (FP64 complex: the registers) a step ahead
+    constexpr int AHEAD = sizeof(GT) == 16 ? 1 : 5;
+    GT down[5], down_in;
+#pragma unroll
+    for (int st = 0; st < AHEAD; ++st) down[st] = g_of((SG_DOWN + st) * P + q);
+    if constexpr (AHEAD == 5) down_in = g_of(SG_DOWN_IN * P + q);
     if (lane >= 64 - TL && wave < nw) wD[wave * TL + l] = D;
     const cpx<T> Du = lane_at(D, (lane - TL) * 4);
     __syncthreads();
-    const int QW = 64 >> lg;
     cpx<T> C = zero;
-    for (int w = 0; w < min(wave, nw); ++w) C = wD[w * TL + l] + mulg(gs[SG_WAVE * P + w * QW], C);
-    cpx<T> d = csel(lane < TL, C, Du + mulg(gs[SG_UP_IN * P + q], C));
+    for (int w = 0; w < min(wave, nw); ++w) C = wD[w * TL + l] + mulg(gw[w], C);
+    cpx<T> d = csel(lane < TL, C, Du + mulg(up_in, C));
 #pragma unroll
     for (int e = 0; e < S; ++e) {
       d = r[e] + mulg(fq[e], d);
@@ -372,18 +403,22 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
     cpx<T> X = zero;
 #pragma unroll
     for (int e = S - 1; e >= 0; --e) X = r[e] + mulg(fq[e], X);
-    st = 0;
-    for (int off = TL; off < 64; off <<= 1, ++st) {
+#pragma unroll
+    for (int st = 0; st < 5; ++st) {
+      const int off = TL << st;
+      if (off >= 64) break;
+      if (st + AHEAD < 5) down[st + AHEAD] = g_of((SG_DOWN + st + AHEAD) * P + q);
       const cpx<T> Xn = lane_at(X, (lane + off) * 4);
-      X = csel(lane + off < 64, X + mulg(gs[(SG_DOWN + st) * P + q], Xn), X);
+      X = csel(lane + off < 64, X + mulg(down[st], Xn), X);
     }
     cpx<T>* wX = wD + nw * TL;
+    if constexpr (AHEAD < 5) down_in = g_of(SG_DOWN_IN * P + q);
     if (lane < TL && wave < nw) wX[wave * TL + l] = X;
     const cpx<T> Xd = lane_at(X, (lane + TL) * 4);
     __syncthreads();
     cpx<T> E = zero;
-    for (int w = nw - 1; w > wave; --w) E = wX[w * TL + l] + mulg(gs[SG_WAVE * P + w * QW], E);
-    cpx<T> xv = csel(lane + TL >= 64, E, Xd + mulg(gs[SG_DOWN_IN * P + q], E));
+    for (int w = nw - 1; w > wave; --w) E = wX[w * TL + l] + mulg(gw[w], E);
+    cpx<T> xv = csel(lane + TL >= 64, E, Xd + mulg(down_in, E));
     // every thread has read its neighbours' rows (two barriers ago)
 #pragma unroll
     for (int e = S - 1; e >= 0; --e) {
@@ -399,8 +434,8 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
     }
   }
   if (STEP || g.part != nullptr) {
-    __syncthreads();  // the lines are stored: their LDS holds the reduction
-    rx_block_store<7>(s, reinterpret_cast<double*>(buf), g.part + 7 * (long long)blockIdx.x);
+    if constexpr (!STEP) __syncthreads();
+    rx_block_total<7>(red, g.part + 7 * (long long)blockIdx.x);
   }
 }
 

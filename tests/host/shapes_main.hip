@@ -48,6 +48,10 @@ static void lengths(const char* prec) {
         check(x->lds <= kRLds, "x LDS", prec, n, n1, n2, (long long)x->lds);
         check(r_threads<T>(a, x->xt.np, false) <= x->threads, "x FFT", prec, n, n1, n2, x->threads);
       }
+      // the x sweep leaves room for a second block on a CU wherever both lines of a pair and a
+      // line's twiddles do (a few hundred bytes of carries and sums aside)
+      if (c.blocks && !a.blue() && a.n <= (sizeof(T) == 8 ? 1500 : 3000))
+        check(c.lds <= 81920, "x LDS of two blocks", prec, n, n1, n2, (long long)c.lds);
       if (c.blocks) {
         check_sweep(c.sweep(), "x sweep", prec, n, n1, n2, r_max_threads<T>());
         check(c.sweep().threads <= c.threads, "x sweep waves", prec, n, n1, n2, c.sweep().threads);

@@ -61,7 +61,21 @@ static void lengths(const char* prec) {
   }
 }
 
+// Strided lines past 2048 rows have no register sweep; many of them run one thread per line.
+template <typename T>
+static void columns(const char* prec) {
+  for (int n : {2052, 2100}) {
+    check(SweepLaunch<T>::cfg(2048, 182, 181, 182).S != 0, "2048 rows", prec, 2048, 182, 181, 0);
+    check(SweepLaunch<T>::cfg(n, 182, 181, 182).S == 0, "past 2048 rows", prec, n, 182, 181, 0);
+    check(gen_size_ok<T>(n), "accepted", prec, n, 182, 181, 0);
+    check(GLaunch<T>::cn_by_columns(n, true, 182 * 181), "by columns", prec, n, 182, 181, 0);
+    check(!GLaunch<T>::cn_by_columns(n, true, 18 * 22), "by tiles", prec, n, 18, 22, 0);
+  }
+}
+
 int main() {
+  columns<float>("fp32");
+  columns<double>("fp64");
   lengths<float>("fp32");
   lengths<double>("fp64");
   printf("%s %lld checks, %lld violations\n", bad ? "bad" : "ok", checked, bad);

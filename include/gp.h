@@ -220,9 +220,11 @@ int gp_history_capacity(void);
 /* Wait for the context's stream; reports the sticky non-finite flag. */
 gp_status gp_sync(gp_ctx* ctx);
 
-/* Step loops of at least 8 steps replay a captured HIP graph of 8 steps (captured once
- * per time direction, re-captured after gp_set_couplings); enable = 0 launches every
- * pass directly.  Default: enabled.  Timing (below) always launches directly. */
+/* Step loops replay captured HIP graphs of 8, 4, 2 and 1 steps (captured once per time
+ * direction and length, re-captured after gp_set_couplings); enable = 0 launches every
+ * pass directly, and a program may capture such calls into a graph of its own on grids with
+ * a run-time-length axis: each replay is then the whole call, records included.  Default:
+ * enabled.  Timing (below) always launches directly. */
 gp_status gp_use_graphs(gp_ctx* ctx, int enable);
 
 /* Optional per-pass timing (profiling and benchmarks).  With a non-zero mask, every

@@ -189,9 +189,10 @@ Layout make_layout(const gp_params* p, unsigned host = 0, bool batch = false) {
                   : gen_long_plan<float>(ns0[a], &L.lg[a]);
   L.lx = lng[0];
   L.ly = lng[1];
-  // one-line y axes past a tile: segmented when there are enough column segments to fill
-  // the GPU (the summary walks each with one thread; fewer ran slower than the transposed
-  // sweep: 1500^2 FP32 0.12 -> 0.22 ms, while 8192^2 went 3.07 -> 2.75 ms)
+  // one-line y axes past the register sweeps (2048 rows): segmented when there are enough
+  // column segments to fill the GPU (the summary walks each with one thread; fewer ran slower
+  // than the transposed sweep, 1500^2 FP32 0.12 -> 0.22 ms before it had the register sweep,
+  // while 8192^2 went 3.07 -> 2.75 ms)
   if (!L.ly && p->geom != GP_3D && L.generic && !L.sw[1].S && L.n1 > kTileMaxN) {
     GLong sg{};
     if (gen_seg_split(L.n1, &sg.sn, &sg.nseg) &&
@@ -253,7 +254,8 @@ Layout make_layout(const gp_params* p, unsigned host = 0, bool batch = false) {
                            : GLaunch<float>::cn_blocks(
                                      L.n1, L.n0, !GLaunch<float>::y2d_transposed(L.n1)));
     // a scratch grid for the one-thread-per-line sweeps (3D grids whose y or z sweep has
-    // many lines longer than a tile) and for the transposed 2D y sweep of long lines
+    // many lines longer than a tile and no register sweep) and for the transposed 2D y sweep
+    // of long lines
     L.gscr = p->geom == GP_3D
                  ? ((!L.sw[1].S && GLaunch<float>::cn_by_columns(L.n1, true, L.n0 * L.n2)) ||
                     (!L.sw[2].S && GLaunch<float>::cn_by_columns(L.n2, true, L.n0 * L.n1)))
@@ -502,8 +504,8 @@ FinArgs fin_args(const gp_ctx* c, int sel) {
   return a;
 }
 
-// The outstanding real-time finalisation, if any, as its own launch(es).  Every entry
-// point other than the real-time step calls this first.
+// The outstanding finalisation, if any, as its own launch(es).  Every entry point other than
+// the step calls calls this first.
 gp_status settle(gp_ctx* c) {
   if (!c->fin_pending) return GP_OK;
   c->fin_pending = false;
@@ -529,11 +531,17 @@ struct Passes {
   // factor table of axis a, set k (0: imaginary time, 1: real time, 2: adjoint sweep)
   static const cpx<T>* cn(gp_ctx* c, int a, int k) { return c->at<cpx<T>>(c->L.o_cn[a][k]); }
 
-  // ------------------------------------------- run-time-length passes (gp_generic.hpp)
-  // The same step as the specialised passes, in simpler launches: the x R2C, the y FFT,
-  // the z convolution and the inverse y FFT (2D: the y convolution), the x C2R into a
-  // real Phi grid, the phase in place, then the x, y and z sweeps; the finalisation runs
-  // after every step.
+  // ------------------------------------------------------------ run-time-length passes
+  // The same step as the specialised passes.  Where an axis has them, its passes are those of
+  // gp_rx.hpp (x: k_rr2c; k_rc2r, which takes the half spectrum through Phi, the phase and the
+  // x sweep without storing Phi), gp_rfft.hpp (k_rlines: y FFTs, z convolution; 2D: the y
+  // convolution) and gp_sweep.hpp (k_sweep: y and z sweeps); the kernels of gp_generic.hpp run
+  // the others: the x C2R into a real Phi grid, the phase with the x sweep, tiled or segmented
+  // sweeps, the four-step FFT of long 2D axes.
+  // The finalisation of a step rides in the next step's k_rr2c (the second of two stages in
+  // its forward y lines) while that pass writes the other x-partial buffer, as on specialised
+  // lengths (g_folds); without such passes, and under per-pass timing, it is a launch of its
+  // own after every step.  Calls without graphs end settled (run_steps).
   // long 2D axes: stage twiddles of the A- (q = 0) and B-point (q = 1) plans, W_N^m (q = 2)
   static const cpx<T>* ltw(gp_ctx* c, int a, int q) { return c->at<cpx<T>>(c->L.o_ltw[a][q]); }
   static const RProgram* rprog(gp_ctx* c, int a, int kind) {

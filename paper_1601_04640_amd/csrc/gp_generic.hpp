@@ -4,7 +4,8 @@
 // length, the FFT's radix plan and the tile shapes are kernel arguments, so one set of
 // kernels serves every such grid.  The main path of a step is in gp_rx.hpp (x passes),
 // gp_rfft.hpp (y and z lines) and gp_sweep.hpp (y and z sweeps); the kernels here run what
-// those do not take: long 2D axes, axes of a single radix, lines past their LDS.
+// those do not take: long 2D axes, axes of 4 to 16 points, lines past their LDS, sweeps past
+// 2048 rows or 4 GiB.
 //
 // The step is the same split-step as the specialised passes ("Solution method": the
 // dipolar term by the convolution theorem, then the Crank-Nicolson sweeps; "Summary of

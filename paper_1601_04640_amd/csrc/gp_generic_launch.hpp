@@ -117,9 +117,11 @@ struct GLaunch {
     }
     return cn_blocks(n0, n1 * n2, false);
   }
-  // CN sweeps: kg_cn_tile with wpl waves per line (1 up to kTileMaxN points, then one
-  // lane per 8 rows) and cn_tile_lines lines per block, except strided sweeps of many
-  // lines longer than kTileMaxN, which run one thread per line (kg_cn_cols)
+  // CN sweeps without a register sweep (gp_sweep.hpp: strided lines to 2048 rows that span
+  // less than 4 GiB; gp_rx.hpp: most x lines): kg_cn_tile with wpl waves per line (1 up to
+  // kTileMaxN points, then one lane per 8 rows) and cn_tile_lines lines per block, except
+  // strided sweeps of many lines longer than kTileMaxN, which run one thread per line
+  // (kg_cn_cols)
   static int cn_tile_wpl(int n) {
     int w = 1;
     while (n > kTileMaxN && 64 * 8 * w < n) w *= 2;

@@ -108,9 +108,9 @@ struct RAxis {
   bool blue() const { return m != n; }
 };
 
-// Largest radices of the two sets of kernels: FP32 holds every radix up to 16 in 78-108
-// VGPRs; FP64 takes 97-122 with radices up to 10 (4 waves per SIMD) and 115-142 with 11 and
-// 13 (3), so only lengths with such a factor run those.
+// Largest radices of the sets of kernels (besides the one with primes to 31): FP32 holds every
+// radix up to 16 in 75-112 VGPRs; FP64 takes 87-128 with radices up to 10 (4 waves per SIMD)
+// and 117-152 with 11 and 13 (3), so only lengths with such a factor run those.
 template <typename T>
 constexpr int r_max_radix(bool big) { return sizeof(T) == 4 ? 16 : big ? 13 : 10; }
 

@@ -250,9 +250,11 @@ template <typename F>
 RXCfg x_shape(const RAxis& a, int n1, int n2, F size) {
   RXCfg best;
   if (a.k < 1 || (double)a.n * (kWide + 1) * sizeof(cpx<T>) >= 2147483648.0) return best;
-  // longer lines leave a block few pairs; the kernels of gp_generic.hpp are faster if they
-  // have the radices (2500^2 FP32 36 + 28 + 88 us, 38 + 126 here; 2048^2 22 + 18 + 41 and
-  // 22 + 53)
+  // Longer lines leave a block one pair: FP32 ones whose radices gp_generic.hpp has written out
+  // run its kernels, which were ahead while the sweep's tables stood beside the twiddles (2500^2
+  // 36 + 28 + 88 us, 38 + 126 here).  Without them there these passes are ahead to some 4000
+  // points (a step of 2500^2 284 us with gp_generic.hpp and 249 here, 3200x1500 157 and 149,
+  // 4096^2 590 and 599); the line has not been moved.
   if (a.n > 2048 && seven_smooth(a.n)) return best;
   const int pairs = (n1 + 1) / 2;
   for (int np = kWide / 2; np >= 1; np /= 2) {

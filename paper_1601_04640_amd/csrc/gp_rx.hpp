@@ -261,6 +261,11 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
   __syncthreads();
   const long long row = ((long long)k * n1 + j0) * N;  // first point of the tile
   const unsigned tl = (unsigned)lines * (unsigned)N;
+  // the factors, fetched ahead of psi and V (400^3 FP32 1539 us a step, 1523 so; FP64 complex
+  // ones after them, for the registers)
+  Prefetch<GT, 4> pf;
+  constexpr bool EARLY = sizeof(GT) <= 8;
+  if constexpr (STEP && EARLY) pf.load(P * S, f_of);
   double s[7] = {0, 0, 0, 0, 0, 0, 0};
   const double z = (k - xt.n2 / 2) * g.h2;
   // both lines of a pair at a point: sums of scale psi, the phase, Phi
@@ -330,11 +335,10 @@ __global__ void __launch_bounds__(r_max_threads<T>(), (sizeof(T) == 8 && MAXR > 
     s[6] = z * z * s[0];
   }
   // the gains of the sweep's scans: each of the chunk's own once, straight from L2
-  Prefetch<GT, 4> pf;
   GT up[5], up_in{};
   const int q = STEP ? min(tid >> lg, P - 1) : 0;
   if constexpr (STEP) {
-    pf.load(P * S, f_of);
+    if constexpr (!EARLY) pf.load(P * S, f_of);
 #pragma unroll
     for (int st = 0; st < 5; ++st) up[st] = g_of((SG_UP + st) * P + q);
     up_in = g_of(SG_UP_IN * P + q);

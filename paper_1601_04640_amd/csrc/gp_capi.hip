@@ -176,10 +176,16 @@ Layout make_layout(const gp_params* p, unsigned host = 0, bool batch = false) {
     // The register sweeps are ahead from 256 points in FP32 (256^2: 5.1 us against 6.5, 256^3
     // 45-48 against 46-51, 480^3 380 against 817) and from 128 points in FP64 where the grid
     // fills the GPU (128^3 11.0-12.6 against 12.7-15.2, 256^3 91-93 against 94); shorter or
-    // fewer lines wait on the scan (FP64 64^3 5.7 against 4.3, 512x384 7.2 against 6.6).
+    // fewer lines wait on the scan (FP64 64^3 5.7 against 4.3, 512x384 7.2 against 6.6).  On
+    // grids that fill the GPU a block's waves have to load the SIMDs alike: FP64 blocks of 3, 5
+    // and 6 waves lose (y and z of 192^3 39 + 42 us against 38 + 40, 320^3 225 + 247 against 211 +
+    // 229, 384^3 402 + 467 against 352 + 411; with 4 or 8, 240^3 74 + 71 against 74 + 73), FP32
+    // ones of 5 (320^3 113 + 106 against 101 + 93; with 6, 384^3 183 + 215 against 181 + 225).
     for (int a = 1; a < 3 && !L.generic; ++a) {
-      const int n = a == 1 ? L.n1 : L.n2;
-      if (batch || n < (fp64 ? 128 : 256) || (fp64 && L.sw[a].blocks < 512)) L.sw[a] = SweepCfg{};
+      const int n = a == 1 ? L.n1 : L.n2, waves = L.sw[a].threads / 64;
+      const bool ahead = fp64 ? n >= 128 && L.sw[a].blocks >= 512 && 16 % waves == 0
+                              : n >= 256 && !(L.sw[a].S == 16 && waves % 2);
+      if (batch || !L.sw[a].S || !ahead) L.sw[a] = SweepCfg{};
     }
   }
   const int ns0[2] = {L.n0, L.n1};
